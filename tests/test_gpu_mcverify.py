@@ -8,6 +8,8 @@ bit), every collision flag and the success counts agree.  2D, 3D and the 6D
 steering cubics.  Then what the estimate says about the front: on the 3D
 workload the plans of lower drift fly with smaller localisation errors.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -105,6 +107,53 @@ def test_mc_noise_free_and_errors():
         mpap.mpap_mc_verify(dg, path, dt=0.0)
     res.close()
     dg.close()
+
+
+@pytest.mark.parametrize("rollouts", [1, 17, 4096, 4097, 8192, 8193, 32768, 32769, 65536, 65537])
+@pytest.mark.parametrize("case", ["plain", "many boxes", "always a fix", "far away"])
+def test_mc_every_lane_split(rollouts, case):
+    """Flights from both ends and the middle of a launch against the oracle,
+    at the edges of the ranges that spread a flight over 16, 8, 4, 2 and 1
+    lanes; with more boxes than one lane's list holds, with fixes at every
+    step (q_min 0), and with blobs that subtract and are far narrower than a
+    step of the flight, far from the origin.  Same tolerance as compare()."""
+    dim = 2 if rollouts in (4096, 4097, 65537) else 3
+    env = synth.plain2d(3, n=400) if dim == 2 else synth.plain3d(3, n=400)
+    kw = {}
+    if case == "many boxes":
+        rng = np.random.default_rng(1)
+        lo = rng.uniform(0.0, 1.0, (150, dim)).astype(np.float32)
+        hi = (lo + rng.uniform(0.005, 0.05, (150, dim))).astype(np.float32)
+        env = dataclasses.replace(env, box_lo=lo, box_hi=hi)
+    elif case == "always a fix":
+        kw["q_min"] = 0.0
+    elif case == "far away":
+        sigma, amp = env.blob_sigma.copy(), env.blob_amp.copy()
+        sigma[::5] = np.float32(0.002)
+        amp[1::4] = np.float32(-0.3)
+        shift = np.float32(1000.0)
+        env = dataclasses.replace(
+            env, pos=env.pos + shift, goal=env.goal + shift, box_lo=env.box_lo + shift,
+            box_hi=env.box_hi + shift, blob_mu=env.blob_mu + shift, blob_sigma=sigma, blob_amp=amp)
+        kw["q_min"] = 0.5
+    # three straight hops (flown whether the roadmap has these edges or not)
+    path = np.array([0, 7, 11, 5], np.int32)
+    mp = mc.MCParams(rollouts=rollouts, dt=0.01, speed=2.0, **kw)
+    p, v, a = mc.nominal_segments(env.pos[path], mp.f64("speed"), mp.f64("dt"))
+    ids = np.unique(np.concatenate([np.arange(min(rollouts, 24)), [rollouts // 2],
+                                    np.arange(max(rollouts - 24, 0), rollouts)]))
+    want = mc.rollouts(p, v, a, mp, env.blob_mu, env.blob_sigma, env.blob_amp, env.box_lo,
+                       env.box_hi, rollout_ids=ids)
+    radius = env.radius
+    goal_radius = max(env.goal_radius, 0.4)
+    dg = mpap.mpap_build_graph(dataclasses.replace(env, goal_radius=goal_radius), radius=radius)
+    st, got, col = mpap.mpap_mc_verify(dg, path, rollouts=rollouts, dt=0.01, speed=2.0, **kw)
+    dg.close()
+    rel = np.abs(got[ids] - want.max_err) / np.maximum(want.max_err, 1e-300)
+    assert rel.max() <= 1e-9, (rel.max(), int(ids[rel.argmax()]))
+    assert np.array_equal(col[ids], want.collided)
+    assert st["collision_free"] == int((~col).sum())
+    assert st["within_bound"] == int((got <= mp.f64("err_bound")).sum())
 
 
 def test_lower_drift_plans_fly_with_smaller_errors():
