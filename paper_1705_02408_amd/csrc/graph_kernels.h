@@ -108,12 +108,17 @@ __global__ void k_scan_sums(int *bsum, int nb);
 __global__ void k_scan_apply(const int *in, long long n, const int *bsum, int *out);
 __global__ void k_add_i32(int *p, long long n, int add);
 __global__ void k_zero_i32(int *p, long long n);
-// surrogate inputs per edge (16 bf16) and the 8-point estimate of the mean
-// of (1 - q) along it (base, nullable)
-__global__ void k_edge_features(BuildArgs g, int n, const int *row_ptr, const int *col,
-                                const float *cost, uint16_t *X, float *base);
-__global__ void k_edge_features_pairs(BuildArgs g, int n, const int *row_ptr, const int *col,
-                                      const float *cost, const int *uptr, uint16_t *X,
-                                      float *base);
+// surrogate inputs per edge (16 bf16) of a symmetric 2D or 3D roadmap and the
+// 8-point estimate of the mean of (1 - q) along it; pairs = uptr[n] (half the
+// edges), at least one; node_w: scratch of n floats.  plain: the blobs and
+// positions allow the three-operation division (quality_points): widths
+// within [1e-6, 1e6], coordinates within 1e6 of the origin (no quotient or
+// remainder leaves the normal range where the exponential can tell), and at
+// most kPlainBlobs blobs (their LDS)
+constexpr int kPlainBlobs = 2048;
+void launch_edge_features(const BuildArgs &g, bool plain, int n, long long pairs,
+                          const int *row_ptr, const int *col, const float *cost,
+                          const int *uptr, float *node_w, uint16_t *X, float *base,
+                          hipStream_t s);
 __global__ void k_drift_ratio(long long m, const float *drift, const float *cost,
                               const float *base, float scale, float *t);

@@ -65,6 +65,34 @@ __device__ __forceinline__ int pair_row(const int *uptr, int n, int t) {
     return lo;
 }
 
+// source row of the t-th pair for the lanes of a wave, t rising with the lane:
+// the wave finds the rows of its first and last pair together (64 probes a
+// step), each lane its own between them
+__device__ __forceinline__ int wave_pair_row(const int *uptr, int n, int t) {
+    const int l = lane_id();
+    int ends[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int ti = __shfl(t, i == 0 ? 0 : 63, 64);
+        int lo = 0, span = n;  // the row is in [lo, lo + span)
+        while (span > 1) {
+            const int step = (span + 63) >> 6;
+            const int at = lo + l * step;
+            const uint64_t below = ballot64(l * step < span && uptr[min(at, n - 1)] <= ti);
+            const int last = 63 - (int)__clzll((unsigned long long)below);
+            lo += last * step;
+            span = min(step, span - last * step);
+        }
+        ends[i] = lo;
+    }
+    int lo = ends[0], hi = ends[1];
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (uptr[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
 // index of edge v -> u in row v (rows sorted by target id), -1 if absent
 __device__ __forceinline__ int reverse_edge(const int *row_ptr, const int *col, int v, int u) {
     const int end = row_ptr[v + 1];
@@ -115,33 +143,58 @@ __device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, f
     return (float)acc;
 }
 
-// surrogate inputs of the id-ordered pair (a, b) of length len: x_a (3), x_b
-// (3, zero z in 2D), the length, q at the 8 segment points (k + 1/2)/8, q(x_b);
-// bfloat16.  Returns the 8-point estimate of the mean of (1 - q).
-__device__ __forceinline__ float pair_features(const BuildArgs &gl, int a, int b, float len,
-                                               uint16_t *f) {
-    float xa[3] = {0.f, 0.f, 0.f}, xb[3] = {0.f, 0.f, 0.f}, df[3] = {0.f, 0.f, 0.f};
-    for (int k = 0; k < gl.dim; ++k) {
-        xa[k] = gl.pos[a * gl.dim + k];
-        xb[k] = gl.pos[b * gl.dim + k];
-        df[k] = xb[k] - xa[k];
+// Blobs staged for the float32 quality: 2 sigma^2 in the place of sigma and,
+// for plain blobs (see PlainBlobs), its reciprocal behind the amplitudes.
+template <bool kPlain, int D>
+__device__ __forceinline__ void stage_quality_blobs(const BuildArgs &g, float *blob) {
+    for (int i = threadIdx.x; i < g.nblob * D; i += blockDim.x) blob[i] = g.mu[i];
+    for (int i = threadIdx.x; i < g.nblob; i += blockDim.x) {
+        const float s = g.sig[i];
+        const float b = 2.0f * s * s;
+        blob[g.nblob * D + i] = b;
+        blob[g.nblob * (D + 1) + i] = g.amp[i];
+        if constexpr (kPlain) blob[g.nblob * (D + 2) + i] = 1.0f / b;
     }
-    for (int k = 0; k < 3; ++k) {
-        f[k] = f2bf(xa[k]);
-        f[3 + k] = f2bf(xb[k]);
+    __syncthreads();
+}
+
+// q at P points (blob_quality's float32 sums, bit for bit).  Bound by
+// instruction issue: distance, division and exponential.  For plain blobs the
+// division d2 / b is three operations with r = 1 / b rounded: q = d2 r is
+// within one unit of the quotient, d2 - q b is exact in a fused operation,
+// and q + r (d2 - q b) is then the correctly rounded quotient (Markstein,
+// "Computation of elementary functions on the IBM RISC System/6000
+// processor", 1990, theorem 8.4), as the division itself gives it.
+template <bool kPlain, int D, int P>
+__device__ __forceinline__ void quality_points(const float *blob, int nblob,
+                                               const float (&x)[P][D], float (&q)[P]) {
+    const float *two_s2 = blob + nblob * D, *amp = two_s2 + nblob, *inv = amp + nblob;
+#pragma unroll
+    for (int i = 0; i < P; ++i) q[i] = 0.0f;
+#pragma unroll 2
+    for (int j = 0; j < nblob; ++j) {
+        const float b = two_s2[j], am = amp[j];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            float d2 = 0.0f;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                const float t = x[i][k] - blob[j * D + k];
+                d2 = d2 + t * t;
+            }
+            float y;
+            if constexpr (kPlain) {
+                const float r = inv[j];
+                const float q0 = d2 * r;
+                y = __builtin_fmaf(__builtin_fmaf(-q0, b, d2), r, q0);
+            } else {
+                y = d2 / b;
+            }
+            q[i] = q[i] + am * expf(-y);
+        }
     }
-    f[6] = f2bf(len);
-    float acc = 0.0f;
-    for (int j = 0; j < 8; ++j) {
-        const float s = ((float)j + 0.5f) / 8.0f;
-        float p[3] = {0.f, 0.f, 0.f};
-        for (int k = 0; k < gl.dim; ++k) p[k] = xa[k] + s * df[k];
-        const float w = 1.0f - blob_quality(gl, p);
-        f[7 + j] = f2bf(w);
-        acc = acc + w;
-    }
-    f[15] = f2bf(1.0f - blob_quality(gl, xb));
-    return acc * 0.125f;
+#pragma unroll
+    for (int i = 0; i < P; ++i) q[i] = fminf(fmaxf(q[i], 0.0f), 1.0f);
 }
 
 }  // namespace
@@ -535,58 +588,88 @@ __global__ void __launch_bounds__(256) k_zero_i32(int *p, long long n) {
         p[i] = 0;
 }
 
-// Inputs of the learned drift surrogate for edge row u -> col[e]
-// (pair_features of the id-ordered pair, so both directions agree) and, if
-// base is not null, the 8-point estimate.  One thread per edge (its source
-// found by a binary search of row_ptr), so every lane has an edge whatever
-// the node degrees.
-__global__ void __launch_bounds__(256) k_edge_features(BuildArgs g, int n, const int *row_ptr,
-                                                       const int *col, const float *cost,
-                                                       uint16_t *X, float *base) {
+// 1 - q of every node, float32 (the last input of the edges into it)
+template <bool kPlain, int D>
+__global__ void __launch_bounds__(256) k_node_free(BuildArgs g, float *node_w) {
     extern __shared__ float blob[];
-    const BuildArgs gl = stage_blobs(g, blob);
-    const int m = row_ptr[n];
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= m) return;
-    int lo = 0, hi = n - 1;  // source u: last row with row_ptr[u] <= e
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (row_ptr[mid] <= e) lo = mid; else hi = mid - 1;
-    }
-    const int u = lo, v = col[e];
-    const float b8 = pair_features(gl, min(u, v), max(u, v), cost[e], X + (size_t)e * 16);
-    if (base) base[e] = b8;
+    stage_quality_blobs<kPlain, D>(g, blob);
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= g.n) return;
+    float x[1][D], q[1];
+#pragma unroll
+    for (int k = 0; k < D; ++k) x[0][k] = g.pos[v * D + k];
+    quality_points<kPlain, D, 1>(blob, g.nblob, x, q);
+    node_w[v] = 1.0f - q[0];
 }
 
-// The same inputs on a symmetric roadmap, one thread per id-ordered pair,
-// written to both of its edges (uptr as for k_edge_drift_pairs).
+// Inputs of the learned drift surrogate of every edge of a symmetric roadmap
+// (uptr as for the drift): x_a (3), x_b (3, zero z in 2D), the length, 1 - q
+// at the 8 segment points (k + 1/2)/8, 1 - q(x_b); bfloat16; and base, the
+// mean of the eight.  L lanes per id-ordered pair, 8 / L points each; both
+// edges' rows are written by the pair's lanes.  1 - q(x_b) comes from
+// k_node_free: one evaluation a node instead of one a pair.
+template <bool kPlain, int L, int D>
 __global__ void __launch_bounds__(256) k_edge_features_pairs(BuildArgs g, int n,
                                                              const int *row_ptr, const int *col,
                                                              const float *cost, const int *uptr,
-                                                             uint16_t *X, float *base) {
+                                                             const float *node_w, uint16_t *X,
+                                                             float *base) {
     extern __shared__ float blob[];
-    const BuildArgs gl = stage_blobs(g, blob);
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= uptr[n]) return;
-    const int u = pair_row(uptr, n, t);
+    stage_quality_blobs<kPlain, D>(g, blob);
+    constexpr int P = 8 / L;
+    const int pairs = uptr[n];
+    const int i = (int)((blockIdx.x * 256ll + threadIdx.x) / L);
+    // (whole waves: the lanes beyond the last pair repeat it)
+    if ((int)((blockIdx.x * 256ll + (threadIdx.x & ~63)) / L) >= pairs) return;
+    const bool live = i < pairs;
+    const int sub = lane_id() % L, lead = lane_id() - sub;
+    const int t = min(i, pairs - 1);
+    const int u = wave_pair_row(uptr, n, t);
     const int e = row_ptr[u + 1] - (uptr[u + 1] - t);
     const int v = col[e];
-    uint16_t f[16];
-    const float b8 = pair_features(gl, u, v, cost[e], f);
+    const float len = cost[e];
+    float xa[3] = {0.f, 0.f, 0.f}, xb[3] = {0.f, 0.f, 0.f};
+    float x[P][D], w[P];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        xa[k] = g.pos[u * D + k];
+        xb[k] = g.pos[v * D + k];
+        const float df = xb[k] - xa[k];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const float s = ((float)(sub * P + p) + 0.5f) / 8.0f;
+            x[p][k] = xa[k] + s * df;
+        }
+    }
+    quality_points<kPlain, D, P>(blob, g.nblob, x, w);
+    // all eight values in every lane of the pair, in point order
+    float f[8], acc = 0.0f;
+#pragma unroll
+    for (int p = 0; p < P; ++p) w[p] = 1.0f - w[p];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if constexpr (L == 1) f[j] = w[j];
+        else f[j] = __shfl(w[j % P], lead + j / P, 64);
+        acc = acc + f[j];
+    }
+    if (!live) return;
+    const float b8 = acc * 0.125f;
     const int r = reverse_edge(row_ptr, col, v, u);
-    uint4 *xe = reinterpret_cast<uint4 *>(X + (size_t)e * 16);
-    const uint4 w0 = make_uint4(f[0] | ((unsigned)f[1] << 16), f[2] | ((unsigned)f[3] << 16),
-                                f[4] | ((unsigned)f[5] << 16), f[6] | ((unsigned)f[7] << 16));
-    const uint4 w1 = make_uint4(f[8] | ((unsigned)f[9] << 16), f[10] | ((unsigned)f[11] << 16),
-                                f[12] | ((unsigned)f[13] << 16), f[14] | ((unsigned)f[15] << 16));
-    xe[0] = w0;
-    xe[1] = w1;
-    if (base) base[e] = b8;
-    if (r >= 0) {
-        uint4 *xr = reinterpret_cast<uint4 *>(X + (size_t)r * 16);
-        xr[0] = w0;
-        xr[1] = w1;
-        if (base) base[r] = b8;
+    auto two = [](float lo, float hi) { return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16); };
+    const uint32_t word[8] = {two(xa[0], xa[1]), two(xa[2], xb[0]), two(xb[1], xb[2]),
+                              two(len, f[0]),    two(f[1], f[2]),   two(f[3], f[4]),
+                              two(f[5], f[6]),   two(f[7], node_w[v])};
+    uint32_t *xe = reinterpret_cast<uint32_t *>(X + (size_t)e * 16);
+    uint32_t *xr = reinterpret_cast<uint32_t *>(X + (size_t)max(r, 0) * 16);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (k / P == sub) {
+            xe[k] = word[k];
+            if (r >= 0) xr[k] = word[k];
+        }
+    if (sub == 0) {
+        base[e] = b8;
+        if (r >= 0) base[r] = b8;
     }
 }
 
@@ -598,4 +681,40 @@ __global__ void __launch_bounds__(256) k_drift_ratio(long long m, const float *d
                                                      float scale, float *t) {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < m) t[e] = scale * (drift[e] / cost[e] - (base ? base[e] : 0.0f));
+}
+
+template <bool kPlain, int D>
+static void edge_features(const BuildArgs &g, int n, long long pairs, const int *row_ptr,
+                          const int *col, const float *cost, const int *uptr, float *node_w,
+                          uint16_t *X, float *base, hipStream_t s) {
+    const size_t lds = sizeof(float) * (size_t)g.nblob * (D + (kPlain ? 3 : 2));
+    k_node_free<kPlain, D><<<(unsigned)((n + 255) / 256), 256, lds, s>>>(g, node_w);
+    auto blocks = [&](int lanes) { return (unsigned)((pairs * lanes + 255) / 256); };
+    if (pairs <= 262144)
+        k_edge_features_pairs<kPlain, 4, D><<<blocks(4), 256, lds, s>>>(
+            g, n, row_ptr, col, cost, uptr, node_w, X, base);
+    else
+        k_edge_features_pairs<kPlain, 2, D><<<blocks(2), 256, lds, s>>>(
+            g, n, row_ptr, col, cost, uptr, node_w, X, base);
+}
+
+// Lanes per pair: four until the chip is full, then two (more points a lane
+// share each blob's reads).  Measured, inputs and network together, 1 / 2 / 4
+// / 8 lanes: 3D, 5,900 pairs 52 / 38 / 30 / 27 us; 47,500 pairs 60 / 51 / 46 /
+// 48; 177,000 pairs 119 / 111 / 109 / 115; 370,000 pairs 200 / 188 / 191 /
+// 202; 2D, 592,000 pairs 141 / 142 / 151 / 176.  One thread per pair with nine
+// points and the plain division took 209, 218, 279, 445 and 252 us.
+
+void launch_edge_features(const BuildArgs &g, bool plain, int n, long long pairs,
+                          const int *row_ptr, const int *col, const float *cost,
+                          const int *uptr, float *node_w, uint16_t *X, float *base,
+                          hipStream_t s) {
+    if (g.dim == 2 && plain)
+        edge_features<true, 2>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
+    else if (g.dim == 2)
+        edge_features<false, 2>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
+    else if (plain)
+        edge_features<true, 3>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
+    else
+        edge_features<false, 3>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
 }

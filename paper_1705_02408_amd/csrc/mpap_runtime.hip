@@ -279,8 +279,15 @@ int mpap_build_graph(const mpap_env *env, const mpap_graph_params *gp, void *str
         plo[i % dim] = std::min(plo[i % dim], x);
         phi[i % dim] = std::max(phi[i % dim], x);
     }
-    for (int j = 0; j < env->n_blobs; ++j)
-        if (!(env->blob_sigma[j] > 0.0f)) return fail(MPAP_ERR_INVAL, "blob sigma must be > 0");
+    bool plain = env->n_blobs <= kPlainBlobs;
+    for (int k = 0; k < dim; ++k) plain = plain && plo[k] >= -1e6f && phi[k] <= 1e6f;
+    for (int j = 0; j < env->n_blobs; ++j) {
+        const float sg = env->blob_sigma[j];
+        if (!(sg > 0.0f)) return fail(MPAP_ERR_INVAL, "blob sigma must be > 0");
+        plain = plain && sg >= 1e-6f && sg <= 1e6f;
+        for (int k = 0; k < dim; ++k)
+            plain = plain && std::fabs(env->blob_mu[(size_t)j * dim + k]) <= 1e6f;
+    }
     // Grid for Near: cells of edge h >= r (1 + 2^-7), at most 16,000 per axis
     // and max(64, min(2n, 2^30)) in all.  The 2^-7 margin covers the float32 roundings
     // of Cost and of the cell coordinates (relative errors of a few 2^-24
@@ -439,6 +446,7 @@ int mpap_build_graph(const mpap_env *env, const mpap_graph_params *gp, void *str
     // ways), so the in-edge lists are the out-edge lists
     g->rptr = g->optr; g->rsrc = g->ocol; g->rcost = g->ocost; g->rdrift = g->odrift;
     // keep the environment for the surrogate's inputs
+    g->plain_blobs = plain;
     g->dim = dim; g->nbox = env->n_boxes; g->nblob = env->n_blobs;
     g->check_step = gp->check_step; g->reset_q = gp->reset_q; g->radius = gp->radius;
     g->pos = d_pos; g->bmu = d_mu; g->bsig = d_sig; g->bamp = d_amp;
@@ -1295,7 +1303,7 @@ void graph_release(mpap_graph *g) {
     }
     dfree(g->optr); dfree(g->ocol); dfree(g->ocost); dfree(g->odrift);
     dfree(g->nflag); dfree(g->goal_list); dfree(g->qoff); dfree(g->qgoff);
-    dfree(g->pos); dfree(g->bmu); dfree(g->bsig); dfree(g->bamp); dfree(g->feat); dfree(g->sbase); dfree(g->sdrift);
+    dfree(g->pos); dfree(g->bmu); dfree(g->bsig); dfree(g->bamp); dfree(g->feat); dfree(g->sbase); dfree(g->node_w); dfree(g->sdrift);
     dfree(g->blo); dfree(g->bhi);
     dfree(g->vel); dfree(g->elen); dfree(g->rperm); dfree(g->srdrift); dfree(g->uptr);
     delete g;

@@ -124,6 +124,8 @@ struct mpap_graph {
     int32_t *rperm = nullptr;
     float *srdrift = nullptr;
     uint16_t *feat = nullptr;  // [E][16] bf16 surrogate inputs, computed on demand
+    float *node_w = nullptr;   // [n] scratch of the inputs (2D/3D): 1 - q of every node
+    bool plain_blobs = false;  // blobs and positions within launch_edge_features' plain range
     float *sbase = nullptr;    // [E] 8-point estimate of the mean of (1 - q) per edge
     float *sdrift = nullptr;   // [E] surrogate drift (forward edge order)
     // symmetric roadmaps with an environment: uptr[u] = entries v > u in the

@@ -130,6 +130,7 @@ int enqueue_features(mpap_graph *g, hipStream_t st) {
     int r;
     if (!g->feat && (r = dalloc(&g->feat, (size_t)std::max<long long>(g->e, 1) * kMlpIn))) return r;
     if (!g->sbase && (r = dalloc(&g->sbase, std::max<long long>(g->e, 1)))) return r;
+    if (g->dim != 6 && !g->node_w && (r = dalloc(&g->node_w, g->n))) return r;
     if (g->n == 0) return MPAP_OK;
     if (g->dim == 6) {
         if (g->e > 0)
@@ -140,13 +141,10 @@ int enqueue_features(mpap_graph *g, hipStream_t st) {
         a.n = g->n; a.dim = g->dim; a.pos = g->pos; a.nblob = g->nblob; a.mu = g->bmu;
         a.sig = g->bsig; a.amp = g->bamp; a.r = g->radius; a.step = g->check_step;
         a.reset_q = g->reset_q;
-        const size_t lds = sizeof(float) * ((size_t)g->nblob * g->dim + 2 * (size_t)g->nblob);
-        if (g->e > 0 && g->uptr)
-            k_edge_features_pairs<<<div_up(g->e / 2 + 1, 256), 256, lds, st>>>(
-                a, g->n, g->optr, g->ocol, g->ocost, g->uptr, g->feat, g->sbase);
-        else if (g->e > 0)
-            k_edge_features<<<div_up(g->e, 256), 256, lds, st>>>(a, g->n, g->optr, g->ocol,
-                                                                 g->ocost, g->feat, g->sbase);
+        // (2D and 3D roadmaps are symmetric and carry their pair index)
+        if (g->e > 0)
+            launch_edge_features(a, g->plain_blobs, g->n, g->e / 2, g->optr, g->ocol, g->ocost,
+                                 g->uptr, g->node_w, g->feat, g->sbase, st);
     }
     HIP_TRY(hipGetLastError());
     return MPAP_OK;

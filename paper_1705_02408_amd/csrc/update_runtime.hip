@@ -310,6 +310,7 @@ int mpap_graph_add_boxes(const mpap_graph *gc, int32_t n_boxes, const float *box
         return bail(r);
     ng->rptr = ng->optr; ng->rsrc = ng->ocol; ng->rcost = ng->ocost; ng->rdrift = ng->odrift;
     ng->dim = dim; ng->nbox = g->nbox + n_boxes; ng->nblob = g->nblob;
+    ng->plain_blobs = g->plain_blobs;
     ng->check_step = g->check_step; ng->reset_q = g->reset_q; ng->radius = g->radius;
     if ((r = build_pair_index(ng, s))) return bail(r);
     HIP_TRY(hipStreamSynchronize(s));

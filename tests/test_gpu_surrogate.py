@@ -2,6 +2,8 @@
 against the float64 reference on the same bfloat16 tensors, inputs against the
 oracle's features, training, scoring, and the analytic re-walk that judges a
 search on the surrogate's drift (with fallback to the analytic search)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -162,6 +164,27 @@ def test_surrogate_search_is_judged_and_falls_back(road3d):
     assert res2.stats()["judged_failed"] == 1
     res2.close()
     s.close()
+
+
+@pytest.mark.parametrize("dim,n", [(2, 600), (2, 26000), (3, 700), (3, 16000)])
+def test_inputs_of_plain_and_other_blobs_agree(dim, n):
+    """The inputs by the three-operation division (blob widths and coordinates
+    in its range) and by the division itself, bit for bit: the same map with
+    one more blob that adds exactly nothing (amplitude 0) but whose width is
+    out of range.  Roadmaps below and above the size where two lanes instead
+    of four take a pair."""
+    env = synth.plain2d(2, n=n) if dim == 2 else synth.plain3d(2, n=n)
+    more = dataclasses.replace(
+        env, blob_mu=np.concatenate([env.blob_mu, env.blob_mu[:1]]),
+        blob_sigma=np.concatenate([env.blob_sigma, np.float32([2e6])]),
+        blob_amp=np.concatenate([env.blob_amp, np.float32([0.0])]))
+    out = []
+    for e in (env, more):
+        dg = mpap.mpap_build_graph(e)
+        out.append(mpap.mpap_edge_features(dg, with_base=True))
+        dg.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(bits(out[0][1]), bits(out[1][1]))
 
 
 def test_surrogate_gain_on_fine_drift_integration():
