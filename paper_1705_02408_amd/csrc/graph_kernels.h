@@ -94,12 +94,12 @@ __global__ void k_compact_edges(long long m, const int *keep, const int *kscan,
                                 const int *cand_v, const float *cand_c, int *col, float *cost);
 __global__ void k_row_ptr(int n, long long m, const int *cand_off, const int *kscan,
                           const int *keep, int *row_ptr);
-__global__ void k_edge_drift(BuildArgs g, int n, const int *row_ptr, const int *col,
-                             const float *cost, float *drift);
-// symmetric roadmaps: one thread per id-ordered pair, both edges written;
-// uptr[u] = entries v > u in rows before u (k_upper_count + exclusive scan)
-__global__ void k_edge_drift_pairs(BuildArgs g, int n, const int *row_ptr, const int *col,
-                                   const float *cost, const int *uptr, float *drift);
+// symmetric roadmaps: each id-ordered pair evaluated once, both edges written;
+// uptr[u] = entries v > u in rows before u (k_upper_count + exclusive scan);
+// pairs = uptr[n] (half the edges), at least one
+void launch_edge_drift_pairs(const BuildArgs &g, int n, long long pairs, const int *row_ptr,
+                             const int *col, const float *cost, const int *uptr, float *drift,
+                             hipStream_t s);
 __global__ void k_upper_count(int n, const int *row_ptr, const int *col, int *cnt);
 __global__ void k_node_flags(BuildArgs g, uint8_t *flag);
 __global__ void k_flag_list(int n, const uint8_t *flag, unsigned bit, int *list, int *count);

@@ -54,18 +54,8 @@ __device__ __forceinline__ void for_adjacent(const GridArgs &gr, int cx, int cy,
         }
 }
 
-// source row of the t-th id-ordered pair (a, b), a < b, of a symmetric
-// roadmap: the last row u with uptr[u] <= t
-__device__ __forceinline__ int pair_row(const int *uptr, int n, int t) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (uptr[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// source row of the t-th pair for the lanes of a wave, t rising with the lane:
+// source row (the last u with uptr[u] <= t) of the t-th id-ordered pair (a, b),
+// a < b, of a symmetric roadmap for the lanes of a wave, t rising with the lane:
 // the wave finds the rows of its first and last pair together (64 probes a
 // step), each lane its own between them
 __device__ __forceinline__ int wave_pair_row(const int *uptr, int n, int t) {
@@ -120,25 +110,142 @@ __device__ __forceinline__ BuildArgs stage_blobs(const BuildArgs &g, float *blob
     return gl;
 }
 
-// drift of the id-ordered pair (a, b) of length len: sum_j (len/K)(1 - q(mid_j))
+// midpoints whose quality sums one pass over the blobs holds in registers
+constexpr int kDriftRun = 16;
+
+// exp(-x) for 0 <= x <= 1/64: its series to the seventh power (the next term
+// is below 2^-63)
+__device__ __forceinline__ double exp_small(double x) {
+    double p = 1.0 / 5040.0;
+    p = __builtin_fma(-x, p, 1.0 / 720.0);
+    p = __builtin_fma(-x, p, 1.0 / 120.0);
+    p = __builtin_fma(-x, p, 1.0 / 24.0);
+    p = __builtin_fma(-x, p, 1.0 / 6.0);
+    p = __builtin_fma(-x, p, 0.5);
+    p = __builtin_fma(-x, p, 1.0);
+    return __builtin_fma(-x, p, 1.0);
+}
+
+// Drift of the id-ordered pair (a, b) of length len: sum_j (len/K)(1 - q(mid_j))
 // over the K sub-step midpoints x_a + ((j + 1/2)/K)(x_b - x_a), in float64
-// in j order from the float32 positions and length, rounded once to float32
-__device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, float len) {
-    double xa[3] = {0.0, 0.0, 0.0}, df[3] = {0.0, 0.0, 0.0};
-    for (int k = 0; k < gl.dim; ++k) {
-        xa[k] = (double)gl.pos[a * gl.dim + k];
-        df[k] = (double)gl.pos[b * gl.dim + k] - xa[k];
+// in j order from the float32 positions and length, rounded once to float32.
+//
+// Bound by float64 issue.  Along a segment a blob's exponent is quadratic in
+// j, so its values at successive midpoints follow from one exponential, the
+// ratio of the first two and the constant ratio of ratios: two exponentials
+// and three operations a midpoint instead of an exponential (about 45
+// operations) each.  A run of at most sixteen midpoints keeps the error of
+// the products below 2e-14 relative, far below the final rounding.  Where an
+// exponent is so large that the first value would underflow the run is
+// evaluated point by point, and blobs too far from all segments of the wave
+// to reach the last bit of q are left out.  L lanes share a pair's blobs when
+// there are too few pairs to fill the chip.  Every lane of the wave calls
+// (live: it holds a pair).
+template <int L, int D>
+__device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, float len,
+                                            bool live) {
+    const int sub = lane_id() % L;
+    double xa[D], df[D];
+    float xaf[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        xaf[k] = gl.pos[a * D + k];
+        xa[k] = (double)xaf[k];
+        df[k] = (double)gl.pos[b * D + k] - xa[k];
     }
     int K = (int)ceilf(len / gl.step);
     if (K < 1) K = 1;
     const double dK = (double)K;
     const double w = (double)len / dK;
+    // runs of equal length (a multiple of four) for the longest pair of the wave
+    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(live ? K : 1));
+    const int runs = (kmax + kDriftRun - 1) / kDriftRun;
+    const int run = ((kmax + runs - 1) / runs + 3) & ~3;
+    double dl[D], c2 = 0.0;  // the step between midpoints and its square
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        dl[k] = df[k] / dK;
+        c2 = __builtin_fma(dl[k], dl[k], c2);
+    }
+    // every point lies within len (and the roundings) of x_a
+    const float reach = len * 1.0001f;
     double acc = 0.0;
-    for (int j = 0; j < K; ++j) {
-        const double s = ((double)j + 0.5) / dK;
-        double p[3];
-        for (int k = 0; k < gl.dim; ++k) p[k] = xa[k] + s * df[k];
-        acc = acc + w * (1.0 - blob_quality_f64(gl, p));
+    for (int j0 = 0; j0 < kmax; j0 += run) {
+        double q[kDriftRun];
+#pragma unroll
+        for (int i = 0; i < kDriftRun; ++i) q[i] = 0.0;
+        const double s0 = ((double)j0 + 0.5) / dK;
+        double x0[D];
+#pragma unroll
+        for (int k = 0; k < D; ++k) x0[k] = xa[k] + s0 * df[k];
+        for (int j = sub; j < gl.nblob; j += L) {
+            const float sg = gl.sig[j], am = gl.amp[j];
+            float d2f = 0.0f, xs = 0.0f;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                const float mu = gl.mu[j * D + k];
+                const float t = xaf[k] - mu;
+                d2f = __builtin_fmaf(t, t, d2f);
+                xs += fabsf(xaf[k]) + fabsf(mu);
+            }
+            // exponent (base 2) at the nearest the segment can come, low by
+            // far more than its roundings
+            const float near = fmaxf(__builtin_amdgcn_sqrtf(d2f) * 0.9999f - reach - xs * 0x1p-20f, 0.0f);
+            const float y = 0.7213f * __builtin_amdgcn_rcpf(sg * sg) * (near * near);
+            // (negated: NaN stays in)
+            if (ballot64(live && !(fabsf(am) * __builtin_amdgcn_exp2f(-y) < 0x1p-66f)) == 0) continue;
+            const double s = (double)sg, amp = (double)am;
+            // 1 / (2 sigma^2) by two Newton steps (NaN where that fails: the
+            // run is then evaluated point by point, with the division)
+            const double two_s2 = 2.0 * (s * s);
+            double inv = __builtin_amdgcn_rcp(two_s2);
+            inv = __builtin_fma(__builtin_fma(-two_s2, inv, 1.0), inv, inv);
+            inv = __builtin_fma(__builtin_fma(-two_s2, inv, 1.0), inv, inv);
+            double d2 = 0.0, g = 0.0;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                const double t = x0[k] - (double)gl.mu[j * D + k];
+                d2 = __builtin_fma(t, t, d2);
+                g = __builtin_fma(t, dl[k], g);
+            }
+            const double e0 = d2 * inv;                              // exponent at the first point
+            const double e1 = __builtin_fma(2.0, g, c2) * inv;       // to the second
+            const double e2 = 2.0 * c2 * inv;                        // and its growth
+            if (ballot64(live && !(e0 <= 690.0 && fabs(e1) <= 600.0 && e2 <= 0x1p-6)) == 0) {
+                double E = amp * exp(-e0), R = exp(-e1);
+                const double C = exp_small(e2);
+#pragma unroll
+                for (int i0 = 0; i0 < kDriftRun; i0 += 4)
+                    if (i0 < run) {
+#pragma unroll
+                        for (int i = i0; i < i0 + 4; ++i) {
+                            q[i] += E;
+                            E *= R;
+                            R *= C;
+                        }
+                    }
+            } else {
+                for (int i = 0; i < run; ++i) {
+                    const double si = ((double)(j0 + i) + 0.5) / dK;
+                    double t2 = 0.0;
+#pragma unroll
+                    for (int k = 0; k < D; ++k) {
+                        const double t = xa[k] + si * df[k] - (double)gl.mu[j * D + k];
+                        t2 = t2 + t * t;
+                    }
+                    const double v = amp * exp(-t2 / two_s2);
+#pragma unroll
+                    for (int k = 0; k < kDriftRun; ++k) q[k] += k == i ? v : 0.0;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kDriftRun; ++i) {
+            double v = q[i];
+#pragma unroll
+            for (int o = 1; o < L; o <<= 1) v += __shfl_xor(v, o, 64);
+            if (i < run && j0 + i < K) acc = acc + w * (1.0 - fmin(fmax(v, 0.0), 1.0));
+        }
     }
     return (float)acc;
 }
@@ -431,41 +538,31 @@ __global__ void __launch_bounds__(256) k_row_ptr(int n, long long m, const int *
     row_ptr[u] = (o < m) ? kscan[o] : (m > 0 ? kscan[m - 1] + keep[m - 1] : 0);
 }
 
-// drift of edge row u -> col[e] (pair_drift of the id-ordered pair: the same
-// value for both directions of an edge)
-__global__ void __launch_bounds__(256) k_edge_drift(BuildArgs g, int n, const int *row_ptr,
-                                                    const int *col, const float *cost,
-                                                    float *drift) {
-    extern __shared__ float blob[];  // mu[nblob*dim], sig[nblob], amp[nblob]
-    const BuildArgs gl = stage_blobs(g, blob);
-    // one thread per edge; its source u: last row with row_ptr[u] <= e
-    const int m = row_ptr[n];
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= m) return;
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (row_ptr[mid] <= e) lo = mid; else hi = mid - 1;
-    }
-    const int u = lo, v = col[e];
-    drift[e] = pair_drift(gl, min(u, v), max(u, v), cost[e]);
-}
-
-// The same drift on a symmetric roadmap (rows sorted by target id), one
-// thread per id-ordered pair: the t-th pair's value is evaluated once and
-// written to both of its edges.  uptr[u] counts the entries v > u of the
-// rows before u (uptr[n] pairs in all).
-__global__ void __launch_bounds__(256) k_edge_drift_pairs(BuildArgs g, int n, const int *row_ptr,
+// The drift of every edge of a symmetric roadmap (rows sorted by target id,
+// the same value both ways), L lanes per id-ordered pair: the t-th pair's
+// value is evaluated once and written to both of its edges.  uptr[u] counts
+// the entries v > u of the rows before u (uptr[n] pairs in all).  Measured
+// against one thread per pair and an exponential per midpoint: 2,424 -> 474
+// us (3D, 50,000 samples, 80 blobs, 972,000 pairs) and 110 -> 17 us (2D,
+// 2,000 samples, 30 blobs, 21,000 pairs).  Three waves per SIMD: four spill
+// 49 registers (595 us).
+template <int L, int D>
+__global__ void __launch_bounds__(256, 3) k_edge_drift_pairs(BuildArgs g, int n, const int *row_ptr,
                                                           const int *col, const float *cost,
                                                           const int *uptr, float *drift) {
     extern __shared__ float blob[];
     const BuildArgs gl = stage_blobs(g, blob);
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= uptr[n]) return;
-    const int u = pair_row(uptr, n, t);
+    const int pairs = uptr[n];
+    const int i = (int)((blockIdx.x * 256ll + threadIdx.x) / L);
+    // (whole waves: the lanes beyond the last pair repeat it)
+    if ((int)((blockIdx.x * 256ll + (threadIdx.x & ~63)) / L) >= pairs) return;
+    const bool live = i < pairs;
+    const int t = min(i, pairs - 1);
+    const int u = wave_pair_row(uptr, n, t);
     const int e = row_ptr[u + 1] - (uptr[u + 1] - t);
     const int v = col[e];
-    const float d = pair_drift(gl, u, v, cost[e]);
+    const float d = pair_drift<L, D>(gl, u, v, cost[e], live);
+    if (!live || lane_id() % L) return;
     drift[e] = d;
     const int r = reverse_edge(row_ptr, col, v, u);
     if (r >= 0) drift[r] = d;
@@ -704,7 +801,6 @@ static void edge_features(const BuildArgs &g, int n, long long pairs, const int 
 // 48; 177,000 pairs 119 / 111 / 109 / 115; 370,000 pairs 200 / 188 / 191 /
 // 202; 2D, 592,000 pairs 141 / 142 / 151 / 176.  One thread per pair with nine
 // points and the plain division took 209, 218, 279, 445 and 252 us.
-
 void launch_edge_features(const BuildArgs &g, bool plain, int n, long long pairs,
                           const int *row_ptr, const int *col, const float *cost,
                           const int *uptr, float *node_w, uint16_t *X, float *base,
@@ -717,4 +813,30 @@ void launch_edge_features(const BuildArgs &g, bool plain, int n, long long pairs
         edge_features<true, 3>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
     else
         edge_features<false, 3>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
+}
+
+template <int D>
+static void drift_pairs(const BuildArgs &g, int n, long long pairs, const int *row_ptr,
+                        const int *col, const float *cost, const int *uptr, float *drift,
+                        hipStream_t s) {
+    const size_t lds = sizeof(float) * ((size_t)g.nblob * D + 2 * (size_t)g.nblob);
+    auto blocks = [&](int lanes) { return (unsigned)((pairs * lanes + 255) / 256); };
+    if (pairs <= 32768)
+        k_edge_drift_pairs<8, D><<<blocks(8), 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
+    else if (pairs <= 131072)
+        k_edge_drift_pairs<2, D><<<blocks(2), 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
+    else
+        k_edge_drift_pairs<1, D><<<blocks(1), 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
+}
+
+// pairs: uptr[n] (half the edges).  Lanes per pair until the chip is full;
+// beyond that the per-pair work that every lane repeats costs more.  Measured
+// with 1 / 2 / 8 lanes: 3D, 5,900 pairs 197 / 104 / 40 us; 30,000 pairs 151 /
+// 85 / 69; 83,000 pairs 154 / 116 / 119; 177,000 pairs 206 / 201 / 214;
+// 2D, 114,000 pairs 34 / 35 / 51; 592,000 pairs 119 / 128 / 237.
+void launch_edge_drift_pairs(const BuildArgs &g, int n, long long pairs, const int *row_ptr,
+                             const int *col, const float *cost, const int *uptr, float *drift,
+                             hipStream_t s) {
+    if (g.dim == 2) drift_pairs<2>(g, n, pairs, row_ptr, col, cost, uptr, drift, s);
+    else drift_pairs<3>(g, n, pairs, row_ptr, col, cost, uptr, drift, s);
 }

@@ -504,13 +504,8 @@ int enqueue_analytic_drift(const mpap_graph *g, float *out, hipStream_t st) {
         a.n = g->n; a.dim = g->dim; a.pos = g->pos; a.nblob = g->nblob; a.mu = g->bmu;
         a.sig = g->bsig; a.amp = g->bamp; a.r = g->radius; a.step = g->check_step;
         a.reset_q = g->reset_q;
-        const size_t lds = sizeof(float) * ((size_t)g->nblob * g->dim + 2 * (size_t)g->nblob);
-        if (g->uptr)
-            k_edge_drift_pairs<<<div_up(g->e / 2 + 1, 256), 256, lds, st>>>(
-                a, g->n, g->optr, g->ocol, g->ocost, g->uptr, out);
-        else
-            k_edge_drift<<<div_up(g->e, 256), 256, lds, st>>>(a, g->n, g->optr, g->ocol,
-                                                              g->ocost, out);
+        // (2D and 3D roadmaps are symmetric and carry their pair index)
+        launch_edge_drift_pairs(a, g->n, g->e / 2, g->optr, g->ocol, g->ocost, g->uptr, out, st);
     }
     HIP_TRY(hipGetLastError());
     return MPAP_OK;

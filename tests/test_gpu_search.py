@@ -282,6 +282,47 @@ def test_build_graph_matches_oracle(dim, n, seed):
     assert np.array_equal(got["reset"], ref["reset"])
 
 
+@pytest.mark.parametrize("dim,n,what", [
+    (2, 400, "many points"), (3, 300, "many points"), (2, 400, "narrow blobs"),
+    (3, 300, "narrow blobs"), (2, 400, "far blobs"), (3, 300, "no blobs"),
+    (2, 6000, "few blobs"), (2, 14000, "few blobs"), (3, 9000, "few blobs")])
+def test_drift_along_segments(dim, n, what):
+    """The drift by products along each segment against the oracle's
+    exponential per midpoint: segments of more midpoints than one run, blobs
+    so narrow that their first value would underflow, blobs out of reach, and
+    roadmaps large enough for two lanes and one lane per pair.  The float64
+    sums agree to 2e-13 relative, so the float32 values differ at most by one
+    rounding, and by that in less than 1e-4 of the edges (2e-13 / 2^-24 is
+    3e-6)."""
+    env = synth.plain2d(8, n=n) if dim == 2 else synth.plain3d(8, n=n)
+    kw = dict(goal=env.pos[-1].copy())
+    if what == "many points":
+        kw["check_step"] = float(np.float32(0.0015))
+    elif what == "narrow blobs":
+        sigma = env.blob_sigma.copy()
+        sigma[::2] = np.float32(0.003)
+        kw["blob_sigma"] = sigma
+    elif what == "far blobs":
+        for k in ("pos", "box_lo", "box_hi", "blob_mu"):
+            kw[k] = getattr(env, k) * np.float32(40.0)
+        kw.update(goal=kw["pos"][-1].copy(), radius=env.radius * 40.0,
+                  check_step=env.check_step * 40.0)
+    elif what == "no blobs":
+        kw.update(blob_mu=env.blob_mu[:0], blob_sigma=env.blob_sigma[:0], blob_amp=env.blob_amp[:0])
+    elif what == "few blobs":
+        kw.update(blob_mu=env.blob_mu[:5], blob_sigma=env.blob_sigma[:5], blob_amp=env.blob_amp[:5])
+    env = dataclasses.replace(env, **kw)
+    ref = ograph.build_graph(env)
+    dg = mpap.mpap_build_graph(env)
+    got = dg.export()
+    dg.close()
+    assert np.array_equal(got["col"], ref["col"])
+    ulps = np.abs(bits(got["drift"]).astype(np.int64) - bits(ref["drift"]).astype(np.int64))
+    print(what, ref["col"].size, "edges,", int((ulps > 0).sum()), "differ", flush=True)
+    assert ulps.max() <= 1
+    assert (ulps > 0).sum() <= 1e-4 * ulps.size
+
+
 def near_env(pos, radius, boxes=False, blobs=True):
     """An environment with the given float32 positions: its last node is the
     goal (a build needs one); no boxes unless asked, so its edges are the Near
