@@ -137,9 +137,24 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
         (env->n_boxes > 0 && (!env->box_lo || !env->box_hi)) ||
         (env->n_blobs > 0 && (!env->blob_mu || !env->blob_sigma || !env->blob_amp)))
         return fail(MPAP_ERR_INVAL, "bad obstacle or blob arrays (at most 1024 boxes)");
-    for (long long i = 0; i < 3ll * n; ++i)
-        if (!std::isfinite(env->pos[i]) || !std::isfinite(env->vel[i]))
-            return fail(MPAP_ERR_INVAL, "non-finite state");
+    float plo[3], phi[3], vlo[3], vhi[3];
+    double vmax2 = 0.0;  // the largest squared speed
+    for (int k = 0; k < 3; ++k) {
+        plo[k] = phi[k] = env->pos[k];
+        vlo[k] = vhi[k] = env->vel[k];
+    }
+    for (int i = 0; i < n; ++i) {
+        const float *v = env->vel + 3ll * i;
+        vmax2 = std::max(vmax2, (double)v[0] * v[0] + (double)v[1] * v[1] + (double)v[2] * v[2]);
+    }
+    for (long long i = 0; i < 3ll * n; ++i) {
+        const float x = env->pos[i], v = env->vel[i];
+        if (!std::isfinite(x) || !std::isfinite(v)) return fail(MPAP_ERR_INVAL, "non-finite state");
+        plo[i % 3] = std::min(plo[i % 3], x);
+        phi[i % 3] = std::max(phi[i % 3], x);
+        vlo[i % 3] = std::min(vlo[i % 3], v);
+        vhi[i % 3] = std::max(vhi[i % 3], v);
+    }
     for (int j = 0; j < env->n_blobs; ++j)
         if (!(env->blob_sigma[j] > 0.0f)) return fail(MPAP_ERR_INVAL, "blob sigma must be > 0");
     DeviceInfo di;
@@ -152,12 +167,41 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
           *d_sig = nullptr, *d_amp = nullptr, *ncost = nullptr, *cost = nullptr, *drift = nullptr,
           *elen = nullptr;
     int *nbr = nullptr, *ncnt = nullptr, *rp = nullptr, *col = nullptr, *tmp = nullptr,
-        *err = nullptr;
+        *err = nullptr, *left = nullptr, *far_src = nullptr, *gcell = nullptr, *gslot = nullptr;
+    float4 *spos = nullptr, *svel = nullptr;
+    float *far_tau = nullptr;
+    SteerBlob *blob64 = nullptr;
     uint8_t *flag = nullptr;
+    // grid of the positions: cubic cells of about 16 states, at most 64 an axis
+    GridArgs gr{};
+    double extent = 0.0, pos_vol = 1.0, vel_vol = 1.0;
+    {
+        double side[3], edge = 0.0;
+        for (int k = 0; k < 3; ++k) {
+            side[k] = (double)phi[k] - plo[k];
+            extent += side[k];
+            edge = std::max(edge, side[k]);
+            // (flat sets: a sheet or a line counts as a tenth as deep as wide)
+            vel_vol *= std::max((double)vhi[k] - vlo[k], 1e-3);
+        }
+        edge = std::max(edge, 1e-6);
+        for (int k = 0; k < 3; ++k) pos_vol *= std::max(side[k], 0.1 * edge);
+        const double h = std::max(std::cbrt(pos_vol * 16.0 / n), edge / 64.0);
+        int cells[3];
+        for (int k = 0; k < 3; ++k) {
+            cells[k] = std::min(64, (int)std::floor(side[k] / h) + 1);
+            gr.lo[k] = plo[k];
+        }
+        gr.gx = cells[0]; gr.gy = cells[1]; gr.gz = cells[2];
+        gr.ncell = gr.gx * gr.gy * gr.gz;
+        gr.inv = (float)(1.0 / h);
+    }
     auto cleanup = [&]() {
         dfree(d_pos); dfree(d_vel); dfree(d_blo); dfree(d_bhi); dfree(d_mu); dfree(d_sig);
         dfree(d_amp); dfree(ncost); dfree(cost); dfree(drift); dfree(elen); dfree(nbr);
-        dfree(ncnt); dfree(rp); dfree(col); dfree(tmp); dfree(err); dfree(flag);
+        dfree(ncnt); dfree(rp); dfree(col); dfree(tmp); dfree(err); dfree(flag); dfree(left);
+        dfree(far_src); dfree(far_tau); dfree(blob64);
+        dfree(gcell); dfree(gslot); dfree(spos); dfree(svel); dfree(gr.ccount); dfree(gr.cstart);
     };
     auto bail = [&](int st) {
         cleanup();
@@ -168,7 +212,11 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
         (r = dalloc(&d_sig, nf_)) || (r = dalloc(&d_amp, nf_)) ||
         (r = dalloc(&nbr, (size_t)n * k_out)) || (r = dalloc(&ncost, (size_t)n * k_out)) ||
         (r = dalloc(&ncnt, n)) || (r = dalloc(&rp, n + 1)) || (r = dalloc(&err, 1)) ||
-        (r = dalloc(&flag, n)) || (r = dalloc(&tmp, div_up(n + 1, kScanTile) + 1)))
+        (r = dalloc(&flag, n)) || (r = dalloc(&left, (size_t)n + 1)) ||
+        (r = dalloc(&far_src, (size_t)n + 1)) || (r = dalloc(&far_tau, n)) || (r = dalloc(&blob64, nf_)) || (r = dalloc(&gcell, n)) ||
+        (r = dalloc(&gslot, n)) || (r = dalloc(&spos, n)) || (r = dalloc(&svel, n)) ||
+        (r = dalloc(&gr.ccount, gr.ncell)) || (r = dalloc(&gr.cstart, gr.ncell)) ||
+        (r = dalloc(&tmp, div_up(std::max(n + 1, gr.ncell), kScanTile) + 1)))
         return bail(r);
     hipError_t he = hipSuccess;
     auto cp = [&](void *d, const void *h, size_t bytes) {
@@ -192,7 +240,55 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
     const size_t lds = sizeof(int) * 2048 + 2 * (size_t)kSteerMaxWidth * 8 +
                        sizeof(float) * 6 * (size_t)env->n_boxes +
                        sizeof(int) * (kSteerThreads / 64) * (size_t)env->n_boxes;
-    k_steer_select<<<n, kSteerThreads, lds, s>>>(a, nbr, ncost, ncnt, err);
+    {
+        BuildArgs b{};
+        b.n = n; b.dim = 3; b.pos = d_pos;
+        k_zero_i32<<<div_up(gr.ncell, 256), 256, 0, s>>>(gr.ccount, gr.ncell);
+        k_zero_i32<<<1, 64, 0, s>>>(left + n, 1);
+        k_zero_i32<<<1, 64, 0, s>>>(far_src + n, 1);
+        k_grid_bin<<<div_up(n, 256), 256, 0, s>>>(b, gr, gcell, gslot);
+        if ((r = scan_i32(gr.ccount, gr.cstart, gr.ncell, tmp, s))) return bail(r);
+        k_steer_scatter<<<div_up(n, 256), 256, 0, s>>>(a, gr, gcell, gslot, spos, svel);
+        // States of cost <= tau fill pi^3/6 tau^3 (T^4/12)^(3/2) of the
+        // six-dimensional state space (the volume of an ellipsoid of J)
+        const double T = gp->horizon, dens = n / (pos_vol * vel_vol);
+        const double unit = 5.16771278 * std::pow(T * T * T * T / 12.0, 1.5);
+        const float tau0 = (float)std::min(std::max(std::cbrt(64.0 / (dens * unit)), 1e-30), 1e30);
+        int ex = 0;
+        const bool pow2 = std::frexp(gp->horizon, &ex) == 0.5f && ex > -40 && ex < 40;
+        SteerBounds sb{};
+        float big = 0.0f;
+        for (int k = 0; k < 3; ++k) {
+            sb.plo[k] = plo[k]; sb.phi[k] = phi[k]; sb.vlo[k] = vlo[k]; sb.vhi[k] = vhi[k];
+            big = std::max({big, std::fabs(plo[k]), std::fabs(phi[k]),
+                            gp->horizon * std::fabs(vlo[k]), gp->horizon * std::fabs(vhi[k])});
+        }
+        sb.extent = (float)extent;
+        sb.eps = 1e-4f * big;
+        {
+            const double x = (double)(gp->traj_steps / 2) / gp->traj_steps, h = 6.0 * x * (1.0 - x);
+            sb.vr = h > 0.0 ? (float)(T * (3.0 * x * x - 4.0 * x + 1.0) / h) : 0.0f;
+            sb.rho = h > 0.0 ? (float)(T / h * (1.0 + std::fabs(3.0 * x * x - 2.0 * x) *
+                                                          std::sqrt(vmax2)))
+                             : INFINITY;
+        }
+        const SteerFar far{far_src, far_tau, far_src + n};
+        const size_t boxes = sizeof(float) * 6 * (size_t)env->n_boxes;
+        const size_t nlds = 4 * (size_t)kNearList * 8 + boxes + sizeof(int) * 4 * (size_t)env->n_boxes;
+        const size_t flds = boxes + sizeof(int) * (kFarThreads / 64) * (size_t)env->n_boxes;
+        const int nb = div_up(n, 4), fb = std::min(n, 1024);
+        if (pow2) {
+            k_steer_near<true><<<nb, 256, nlds, s>>>(a, gr, sb, spos, svel, tau0, nbr, ncost, ncnt, far);
+            k_steer_far<true><<<fb, kFarThreads, flds, s>>>(a, gr, sb, spos, svel, tau0, nbr, ncost,
+                                                            ncnt, far, left, left + n);
+        } else {
+            k_steer_near<false><<<nb, 256, nlds, s>>>(a, gr, sb, spos, svel, tau0, nbr, ncost, ncnt, far);
+            k_steer_far<false><<<fb, kFarThreads, flds, s>>>(a, gr, sb, spos, svel, tau0, nbr, ncost,
+                                                             ncnt, far, left, left + n);
+        }
+    }
+    k_steer_select<<<std::min(n, 1024), kSteerThreads, lds, s>>>(a, left, left + n, nbr, ncost, ncnt,
+                                                                 err);
     HIP_TRY(hipGetLastError());
     // row pointers: exclusive scan of the counts, total in rp[n]
     if ((r = scan_i32(ncnt, rp, n, tmp, s))) return bail(r);
@@ -208,8 +304,10 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
     if ((r = dalloc(&col, std::max(e, 1ll))) || (r = dalloc(&cost, std::max(e, 1ll))) ||
         (r = dalloc(&drift, std::max(e, 1ll))) || (r = dalloc(&elen, std::max(e, 1ll))))
         return bail(r);
-    k_steer_compact<<<div_up(n, 256), 256, 0, s>>>(n, k_out, rp, nbr, ncost, ncnt, col, cost);
-    k_traj_drift<<<n, 64, sizeof(float) * 5 * nf_, s>>>(a, rp, col, drift, elen);
+    k_steer_compact<<<div_up(n, 4), 256, 0, s>>>(n, k_out, rp, nbr, ncost, ncnt, col, cost);
+    if (env->n_blobs > 0)
+        k_steer_blobs<<<div_up(env->n_blobs, 256), 256, 0, s>>>(env->n_blobs, d_mu, d_sig, d_amp, blob64);
+    launch_traj_drift(a, blob64, rp, col, drift, elen, s);
     {
         BuildArgs b{};
         b.n = n; b.dim = 3; b.pos = d_pos; b.nblob = env->n_blobs; b.mu = d_mu; b.sig = d_sig;
@@ -247,7 +345,8 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
     g->horizon = gp->horizon; g->traj_steps = gp->traj_steps; g->k_out = k_out;
     g->pos = d_pos; g->vel = d_vel; g->bmu = d_mu; g->bsig = d_sig; g->bamp = d_amp;
     g->blo = d_blo; g->bhi = d_bhi;
-    g->elen = elen;
+    g->elen = elen; g->blob64 = blob64;
+    blob64 = nullptr;
     d_pos = d_vel = d_mu = d_sig = d_amp = elen = d_blo = d_bhi = nullptr;
     cleanup();
     *out = g;
@@ -1303,6 +1402,6 @@ void graph_release(mpap_graph *g) {
     dfree(g->nflag); dfree(g->goal_list); dfree(g->qoff); dfree(g->qgoff);
     dfree(g->pos); dfree(g->bmu); dfree(g->bsig); dfree(g->bamp); dfree(g->feat); dfree(g->sbase); dfree(g->node_w); dfree(g->sdrift);
     dfree(g->blo); dfree(g->bhi);
-    dfree(g->vel); dfree(g->elen); dfree(g->rperm); dfree(g->srdrift); dfree(g->uptr);
+    dfree(g->vel); dfree(g->elen); dfree(g->rperm); dfree(g->srdrift); dfree(g->uptr); dfree(g->blob64);
     delete g;
 }

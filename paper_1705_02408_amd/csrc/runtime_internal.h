@@ -88,6 +88,7 @@ inline int scan_i32(const int *in, int *out, long long n, int *tmp, hipStream_t 
 
 // ------------------------------------------------------------------ graph
 struct Workspace;
+struct SteerBlob;
 
 struct mpap_graph {
     int dev = -1;
@@ -117,6 +118,7 @@ struct mpap_graph {
     // double integrator (dim 6): velocities, steering time, check steps, and
     // the trajectory length of every edge (the drift's length)
     float *vel = nullptr, *elen = nullptr;
+    SteerBlob *blob64 = nullptr;  // dim 6: the blobs widened to float64
     float horizon = 0.f;
     int traj_steps = 0, k_out = 0;
     // directed roadmaps: reverse slot -> forward edge index, and the

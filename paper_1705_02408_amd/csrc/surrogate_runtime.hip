@@ -497,8 +497,7 @@ int enqueue_analytic_drift(const mpap_graph *g, float *out, hipStream_t st) {
     if (!g || !out) return fail(MPAP_ERR_INVAL, "null argument");
     if (!g->pos) return fail(MPAP_ERR_INVAL, "graph has no environment (build it with mpap_build_graph)");
     if (g->n > 0 && g->dim == 6) {
-        k_traj_drift<<<g->n, 64, sizeof(float) * 5 * (size_t)g->nblob, st>>>(
-            steer_view(g), g->optr, g->ocol, out, nullptr);
+        launch_traj_drift(steer_view(g), g->blob64, g->optr, g->ocol, out, nullptr, st);
     } else if (g->n > 0 && g->e > 0) {
         BuildArgs a{};
         a.n = g->n; a.dim = g->dim; a.pos = g->pos; a.nblob = g->nblob; a.mu = g->bmu;

@@ -1,6 +1,8 @@
 """Double-integrator (6D state) roadmaps: the device build against the oracle
 build, the search on the oracle's arrays (shared input) against the oracle
 search, and the learned drift surrogate on 6D edges."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -41,6 +43,59 @@ def test_device_build_matches_oracle(built):
     bad = np.nonzero(bits(got["drift"]) != bits(ref["drift"]))[0]
     assert bad.size == 0, (bad.size, bad[:8])
     assert np.array_equal(got["reset"], ref["reset"])
+
+
+@pytest.mark.parametrize("what", [
+    "two states", "few states", "T not a power of two", "long T, few checks", "short T", "flat",
+    "cluster", "equal states", "many equal states", "at rest", "more blobs than a word",
+    "no boxes or blobs", "outside the cube"])
+def test_device_build_of_uncommon_states(what):
+    """Rows, costs and drifts of roadmaps that take the selection's other
+    branches, against the oracle's: the plain division, shells that thin out
+    or end with every state, lists too long for one wave, more equal costs
+    than one round ranks (the radix selection), sources with no target."""
+    rng = np.random.default_rng(5)
+    n = {"two states": 1, "few states": 30}.get(what, 700)
+    env = synth.plain6d(4, n=n)
+    pos, vel = env.pos.copy(), env.vel.copy()
+    kw = {}
+    if what == "T not a power of two":
+        kw = dict(horizon=0.45, k_out=64)
+    elif what == "long T, few checks":
+        kw = dict(horizon=1.0, traj_steps=7, k_out=5)
+    elif what == "short T":
+        kw = dict(horizon=0.125, traj_steps=255)
+    elif what == "flat":
+        pos[:, 1] = np.float32(0.4)
+    elif what == "cluster":
+        pos[:500] = (0.5 + 0.004 * rng.standard_normal((500, 3))).astype(np.float32)
+        vel[:500] *= np.float32(0.05)
+    elif what == "equal states":
+        pos[20:60], vel[20:60] = pos[20], vel[20]
+    elif what == "many equal states":
+        pos[20:95], vel[20:95] = pos[20], vel[20]
+    elif what == "at rest":
+        vel[:] = 0
+    elif what == "more blobs than a word":
+        kw = dict(blob_mu=np.tile(env.blob_mu, (2, 1)), blob_sigma=np.tile(env.blob_sigma, 2),
+                  blob_amp=np.tile(env.blob_amp, 2) * np.float32(0.4))
+    elif what == "no boxes or blobs":
+        kw = dict(box_lo=env.box_lo[:0], box_hi=env.box_hi[:0], blob_mu=env.blob_mu[:0],
+                  blob_sigma=env.blob_sigma[:0], blob_amp=env.blob_amp[:0])
+    elif what == "outside the cube":
+        pos[::3] += np.float32(0.7)
+    env = dataclasses.replace(env, pos=pos, vel=vel, goal=pos[-1].copy(), goal_radius=0.5, **kw)
+    ref = graph6d.build_graph6d(env)
+    dg = mpap.mpap_build_graph(env)
+    got = dg.export()
+    dg.close()
+    assert np.array_equal(got["row_ptr"], ref["row_ptr"])
+    assert np.array_equal(got["col"], ref["col"])
+    assert np.array_equal(bits(got["cost"]), bits(ref["cost"]))
+    # the float64 sums differ by the order of the blobs' terms and the
+    # exponential, 1e-13 at most: one rounding of the float32 value at most
+    ulps = np.abs(bits(got["drift"]).astype(np.int64) - bits(ref["drift"]).astype(np.int64))
+    assert ulps.size == 0 or ulps.max() <= 1
 
 
 @pytest.mark.parametrize("seed,n", [(1, 1200), (2, 2000)])
