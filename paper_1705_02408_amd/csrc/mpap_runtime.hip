@@ -876,7 +876,8 @@ SearchArgs search_args(const mpap_graph *g, Workspace *w, const SearchPrep &p,
     a.big_front = L.big_front; a.big_children = L.big_children; a.halves_min = L.halves_min;
     a.pool = w->pool; a.pool_cap = w->pool_cap; a.pool_top = w->pool_top; a.nb = w->nb;
     a.minopen = w->minopen; a.gcnt = w->gcnt; a.fo = w->fo; a.mark = w->mark; a.wt = w->wt;
-    a.alist = w->alist; a.acnt = w->acnt; a.mcur = w->mcur; a.F = w->F; a.F_cap = w->F_cap;
+    a.alist = w->alist; a.acnt = w->acnt; a.mcur = w->mcur; a.claim = w->claim;
+    a.queue_cap = (int)(L.lds / 4) - 2 * L.threads - 32; a.F = w->F; a.F_cap = w->F_cap;
     a.arena = w->arena; a.arena_cap = std::min<long long>(w->arena_cap, 0x7ffffff0ll);
     a.part_cnt = w->part_cnt; a.part_open = w->part_open; a.part_step = w->part_step;
     a.bar = w->bar; a.err = w->err; a.out = w->out;

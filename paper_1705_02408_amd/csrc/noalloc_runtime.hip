@@ -158,11 +158,12 @@ extern "C" int mpap_search_noalloc(const mpap_graph *gc, const mpap_search_param
     w.alist = cv.take<int>((size_t)kListRegions * n);
     w.acnt = cv.take<int>(2 * kListRegions);
     w.mcur = cv.take<int>(2 * kListRegions);
+    w.claim = cv.take<int>(2 * kClaimWords);
     w.part_cnt = cv.take<long long>(2 * (size_t)L.nblocks);
     w.part_open = cv.take<long long>(2 * (size_t)L.nblocks);
     w.part_step = cv.take<long long>(2 * (size_t)L.nblocks);
-    w.pool_top = cv.take<unsigned>(1);
-    w.bar = cv.take<unsigned>(1);
+    w.pool_top = cv.take<unsigned>(kBarWords);
+    w.bar = cv.take<unsigned>(kBarWords);
     w.err = cv.take<int>(1);
     w.out = cv.take<long long>(kOutWords);
     w.wstat = cv.take<long long>((size_t)kTraceCap * kTraceWords);

@@ -172,6 +172,7 @@ struct Workspace {
     int *alist = nullptr;
     int *acnt = nullptr;
     int *mcur = nullptr;
+    int *claim = nullptr;
     float4 *F = nullptr;
     int2 *arena = nullptr;
     long long *part_cnt = nullptr, *part_open = nullptr;
@@ -208,7 +209,7 @@ struct Workspace {
 
     void free_all() {
         dfree(pool); dfree(pool_top); dfree(nb); dfree(minopen); dfree(gcnt); dfree(fo);
-        dfree(mark); dfree(wt); dfree(alist); dfree(acnt); dfree(mcur); dfree(F); dfree(arena); dfree(part_cnt);
+        dfree(mark); dfree(wt); dfree(alist); dfree(acnt); dfree(mcur); dfree(claim); dfree(F); dfree(arena); dfree(part_cnt);
         dfree(part_open); dfree(part_step); dfree(bar); dfree(err); dfree(out); dfree(wstat);
         dfree(spill); dfree(spill_flags);
         dfree(g_out); dfree(g_out_node); dfree(g_n); dfree(g_count); dfree(g_total);
@@ -253,10 +254,11 @@ inline int ws_alloc_nodes(Workspace *w, int32_t n, int nblocks) {
     if ((r = dalloc(&w->alist, (size_t)kListRegions * n))) return r;
     if ((r = dalloc(&w->acnt, 2 * kListRegions))) return r;
     if ((r = dalloc(&w->mcur, 2 * kListRegions))) return r;
+    if ((r = dalloc(&w->claim, 2 * kClaimWords))) return r;
     if ((r = dalloc(&w->part_cnt, 2 * (size_t)nblocks))) return r;
     if ((r = dalloc(&w->part_open, 2 * (size_t)nblocks))) return r;
     if ((r = dalloc(&w->part_step, 2 * (size_t)nblocks))) return r;
-    if ((r = dalloc(&w->bar, 1))) return r;
+    if ((r = dalloc(&w->bar, kBarWords))) return r;
     if ((r = dalloc(&w->err, 1))) return r;
     if ((r = dalloc(&w->out, kOutWords))) return r;
     if ((r = dalloc(&w->wstat, (size_t)kTraceCap * kTraceWords))) return r;

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "device_common.h"
+
 // status / error bits written by the device
 constexpr int kStatusOk = 0;
 constexpr int kStatusError = 1;       // see the err word
@@ -25,6 +27,8 @@ constexpr int kWeightClassBase = 128;
 // and (with merges by halves) two of targets the whole workgroup merges: the
 // heavy ones (first), then the rest.
 constexpr int kListRegions = 3 + kWeightClasses;
+constexpr int kClaimGroups = 16;                    // ranges of the single-wave list
+constexpr int kClaimWords = kClaimGroups * kBarLine;  // their counters, a line each
 
 // device output words
 constexpr int kOutWaves = 0;
@@ -110,6 +114,8 @@ struct SearchArgs {
                        // 1+kWeightClasses (heavy) and 2+kWeightClasses
     int *acnt;         // [2 kListRegions] target count of region r at [2 r + wave parity]
     int *mcur;         // [2 kListRegions] next target to merge, same layout
+    int *claim;        // [2][kClaimWords] single-wave claims by wave parity
+    int queue_cap;     // LDS words that select gathers new targets in
     int wcap;          // largest front merged by a single wave (0: none)
     int wmin;          // single-wave merges in iterations with at least wmin small targets
     int wslice;        // LDS bytes of one wave's slice in single-wave merges

@@ -65,6 +65,13 @@ __device__ __forceinline__ long long first_step(float c, float d) {
     return i;
 }
 
+// LDS writes of the wave's lanes visible to its other lanes
+__device__ __forceinline__ void wsync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------------ P1
 // Nodes of the block's range are taken a tile (one per thread) at a time; the
 // nodes whose least open cost is within the threshold go to an LDS list and
@@ -134,12 +141,26 @@ __device__ __forceinline__ void phase_count(const SearchArgs &a, long long istep
 template <bool kSplit>
 __device__ __forceinline__ void phase_select(const SearchArgs &a, long long istep, int wave, long long abase,
                              long long myoff, int lo, int hi, int *list, int *list_off,
-                             int *scan) {
+                             int *scan, int *queue, int queue_cap) {
     const int l = lane_id();
     const int w = threadIdx.x >> 6;
     const int nw = blockDim.x >> 6;
     const unsigned wp = wave_par(wave);
     long long carry = myoff;
+    // New targets gather in LDS, a segment per wave (and list), and go out
+    // with one slot reservation per block and list at the end of the phase:
+    // one a wave of 64 out-edges had a thousand and more reservations an
+    // iteration wait for each other at 12 ns.  A full segment goes out alone.
+    const int cap = queue_cap / ((kSplit ? 2 : 1) * nw);
+    int *const seg0 = queue + w * cap, *const seg1 = queue + (nw + w) * cap;
+    int q0 = 0, q1 = 0;  // queued by this wave
+    auto flush = [&](const int *seg, int n, int counter, int region) {
+        int base = 0;
+        if (l == 0) base = atomicAdd(&a.acnt[counter + wp], n);
+        base = __shfl(base, 0, 64);
+        wsync();
+        for (int i = l; i < n; i += 64) a.alist[(size_t)region * a.n + base + i] = seg[i];
+    };
     for (int tb = lo; tb < hi; tb += blockDim.x) {
         const int v = tb + threadIdx.x;
         const int g = (v < hi) ? a.gcnt[v] : 0;
@@ -221,20 +242,46 @@ __device__ __forceinline__ void phase_select(const SearchArgs &a, long long iste
                 }
                 const uint64_t fs = ballot64(fresh && !big), fb = ballot64(fresh && big);
                 if (fs) {
-                    int base = 0;
-                    if (l == 0) base = atomicAdd(&a.acnt[wp], (int)__popcll(fs));
-                    base = __shfl(base, 0, 64);
-                    if (fresh && !big) a.alist[base + lanes_below(fs)] = x;
+                    if (q0 + 64 > cap) {
+                        flush(seg0, q0, 0, 0);
+                        q0 = 0;
+                        wsync();
+                    }
+                    if (fresh && !big) seg0[q0 + lanes_below(fs)] = x;
+                    q0 += (int)__popcll(fs);
                 }
-                if (fb) {
-                    int base = 0;
-                    if (l == 0) base = atomicAdd(&a.acnt[2 + wp], (int)__popcll(fb));
-                    base = __shfl(base, 0, 64);
-                    if (fresh && big) a.alist[a.n + base + lanes_below(fb)] = x;
+                if (kSplit && fb) {
+                    if (q1 + 64 > cap) {
+                        flush(seg1, q1, 2, 1);
+                        q1 = 0;
+                        wsync();
+                    }
+                    if (fresh && big) seg1[q1 + lanes_below(fb)] = x;
+                    q1 += (int)__popcll(fb);
                 }
             }
         }
         carry += tot;
+        __syncthreads();
+    }
+    // what is left, the block's waves behind each other
+#pragma unroll
+    for (int r = 0; r < (kSplit ? 2 : 1); ++r) {
+        const int q = r == 0 ? q0 : q1;
+        if (l == 0) scan[w] = q;
+        __syncthreads();
+        int before = 0, all = 0;
+        for (int i = 0; i < nw; ++i) {
+            if (i < w) before += scan[i];
+            all += scan[i];
+        }
+        __syncthreads();
+        if (all == 0) continue;  // (the same in every thread)
+        if (threadIdx.x == 0) scan[0] = atomicAdd(&a.acnt[2 * r + wp], all);
+        __syncthreads();
+        const int base = scan[0] + before;
+        const int *seg = r == 0 ? seg0 : seg1;
+        for (int i = l; i < q; i += 64) a.alist[(size_t)r * a.n + base + i] = seg[i];
         __syncthreads();
     }
 }
@@ -864,13 +911,6 @@ __device__ void carve_wave(unsigned char *lds, const SearchArgs &a, WaveLds &w) 
     w.cd = p;
 }
 
-// LDS writes of the wave's lanes visible to its other lanes
-__device__ __forceinline__ void wsync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ int wave_min_i(int v) { return -wave_max_i(-v); }
 
 // segment summaries of the wave's front B[0..n)
@@ -1349,10 +1389,11 @@ __global__ void __launch_bounds__(256) k_search_init(SearchArgs a) {
             a.acnt[i] = 0;
             a.mcur[i] = 0;
         }
-        *a.bar = 0u;
         *a.err = 0;
         for (int i = 0; i < kOutWords; ++i) a.out[i] = 0;
     }
+    for (int i = v; i < kBarWords; i += (int)(gridDim.x * blockDim.x)) a.bar[i] = 0u;
+    for (int i = v; i < 2 * kClaimWords; i += (int)(gridDim.x * blockDim.x)) a.claim[i] = 0;
     for (long long i = v; i < (long long)a.wstat_cap * kTraceWords;
          i += (long long)gridDim.x * blockDim.x)
         a.wstat[i] = 0;
@@ -1425,6 +1466,47 @@ __device__ __forceinline__ void carve_lds(unsigned char *lds, const SearchArgs &
     carve_group(lds, a, s, a.capB, a.capC, (int)blockDim.x, true);
 }
 
+// Targets 0..n-1 of a list handed to the waves of the grid one at a time.
+// Claims at one counter wait for each other (12 ns each: 6 ms of a search
+// of 790,000 small merges), so the list is split in kClaimGroups ranges with
+// a counter each, in lines of their own; a block starts at its range and goes
+// on to the others once that is used up.  Whole waves call.
+struct WaveClaims {
+    int *cur;  // counters, kBarLine words apart
+    int n, g;
+    bool home;  // its own range is not used up
+    __device__ __forceinline__ WaveClaims(int *cursors, int targets, int block)
+        : cur(cursors), n(targets), g(block % kClaimGroups), home(true) {}
+    __device__ __forceinline__ int first(int i) const {
+        return (int)((long long)n * i / kClaimGroups);
+    }
+    // the next target, or -1 when all are claimed
+    __device__ __forceinline__ int next() {
+        for (;;) {
+            if (home) {
+                int k = 0;
+                if (lane_id() == 0)
+                    k = __hip_atomic_fetch_add(cur + g * kBarLine, 1, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                k = first(g) + __shfl(k, 0, 64);
+                if (k < first(g + 1)) return k;
+            }
+            // the next range with targets left, if any (counters only grow)
+            const int i = lane_id() % kClaimGroups;
+            const int used = __hip_atomic_load(cur + i * kBarLine, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t left = ballot64(lane_id() < kClaimGroups && first(i) + used < first(i + 1));
+            if (left == 0) {
+                home = false;
+                return -1;
+            }
+            const uint64_t after = left & ~((2ull << g) - 1ull);
+            g = (int)__ffsll((unsigned long long)(after ? after : left)) - 1;
+            home = true;
+        }
+    }
+};
+
 // kHalves (workgroup-only build): iterations with at least a.halves_min
 // targets merge by halves.  kObj: the objective count of every query (2 or
 // 3), or 0 when it differs between queries.
@@ -1470,6 +1552,9 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                 a.acnt[2 * r + wave_par(wave)] = 0;
                 a.mcur[2 * r + wave_par(wave)] = 0;
             }
+            if constexpr (kWaveMerges)
+                for (int i = 0; i < kClaimGroups; ++i)
+                    a.claim[wave_par(wave) * kClaimWords + i * kBarLine] = 0;
         }
         if (a.early_any) {
             // Alg. 3's loop condition, per query: the loop ends before a
@@ -1540,10 +1625,11 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
             break;
         }
         {
-            MergeLds s;
-            carve_lds(lds, a, s);
-            phase_select<kWaveMerges>(a, i_step, wave, abase, before, lo, hi, s.u_idx, s.u_end,
-                                      s.scan);
+            // (its own view of the LDS: two node lists, scan words, the queue)
+            int *const list = reinterpret_cast<int *>(lds);
+            int *const scan = list + 2 * blockDim.x;
+            phase_select<kWaveMerges>(a, i_step, wave, abase, before, lo, hi, list,
+                                      list + blockDim.x, scan, scan + 32, a.queue_cap);
         }
         if (tr0 && tr) tr[kTrSelectDone] = (long long)wall_clock64();
         grid_barrier(a.bar, G, epoch, a.err, kErrTimeout, kSpinLimit);
@@ -1564,12 +1650,11 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
             // its LDS slice; fronts that outgrow it join the large list
             WaveLds W;
             carve_wave(lds, a, W);
-            for (;;) {
-                int k = 0;
-                if (lane_id() == 0) k = atomicAdd(&a.mcur[wp], 1);
-                k = __shfl(k, 0, 64);
-                if (k >= na) break;
+            WaveClaims claims(a.claim + wp * kClaimWords, na, b);
+            int k = claims.next();
+            while (k >= 0) {
                 const int x = a.alist[k];
+                const int k2 = claims.next();  // claimed while this one merges
                 if ((unsigned)x >= (unsigned)a.n) {
                     if (lane_id() == 0) atomicOr(a.err, kErrTarget);
                 } else if (wave_merge_node<kObj>(a, x, wave, W, wv_cand)) {
@@ -1578,6 +1663,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                     const int kb = atomicAdd(&a.acnt[2 + wp], 1);
                     a.alist[a.n + kb] = x;
                 }
+                k = k2;
             }
             __syncthreads();  // the slices are the workgroup's LDS again
             grid_barrier(a.bar, G, epoch, a.err, kErrTimeout, kSpinLimit);

@@ -181,10 +181,11 @@ __global__ void k_update_words(SearchArgs a) {
         a.mcur[i] = 0;
     }
     for (int i = threadIdx.x; i < kOutWords; i += blockDim.x) a.out[i] = 0;
+    for (int i = threadIdx.x; i < kBarWords; i += blockDim.x) a.bar[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * kClaimWords; i += blockDim.x) a.claim[i] = 0;
     for (long long i = threadIdx.x; i < (long long)a.wstat_cap * kTraceWords; i += blockDim.x)
         a.wstat[i] = 0;
     if (threadIdx.x == 0) {
-        *a.bar = 0u;
         *a.err = 0;
         a.qlast[0] = 0;
         a.qstop[0] = -2;

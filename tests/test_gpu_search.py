@@ -545,6 +545,32 @@ def test_hub_with_many_in_edge_tiles(n_obj, threads, lam, halves):
     dg.close()
 
 
+@pytest.mark.parametrize("threads,wmin", [(256, -1), (512, -1), (1024, -1), (1024, 1)])
+def test_node_with_many_out_edges(threads, wmin):
+    """A row of 12,000 out-edges: the new targets of one wave outgrow its part
+    of the LDS (about 2,400) and go out in several pieces; the next layer's
+    edges share 400 targets, each queued once.  Merges by workgroups of every
+    size and by single waves."""
+    rng = np.random.default_rng(5)
+    wide = 12000
+    edges = [(0, 1, 0.5, 0.1)]
+    edges += [(1, 2 + i, float(c), float(d)) for i, (c, d) in
+              enumerate(zip(rng.uniform(0.5, 1.0, wide), rng.uniform(0.0, 0.3, wide)))]
+    sink = 2 + wide
+    edges += [(2 + i, sink + (i % 400), float(c), 0.05) for i, c in
+              enumerate(rng.uniform(0.5, 1.0, wide))]
+    goal = sink + 400
+    edges += [(sink + i, goal, 0.25, 0.01) for i in range(400)]
+    mask = np.zeros(goal + 1, dtype=np.uint8)
+    mask[goal] = 1
+    g = from_edges(goal + 1, edges, np.zeros(goal + 1, dtype=np.uint8), mask)
+    ref = osearch.search(g, 0.6, 2)
+    dg, res = run(g, 0.6, 2, radius=1.0, lam=4.0, block_threads=threads, wave_min_targets=wmin)
+    check_against_oracle(g, res, ref, 0.6, 2, all_nodes=False, node_stride=7)
+    res.close()
+    dg.close()
+
+
 @pytest.mark.parametrize("seed", [0, 1, 2])
 def test_merges_by_halves_match_the_oracle(road2d, seed):
     """The build with merges by halves forced on the 2,000-sample roadmaps
