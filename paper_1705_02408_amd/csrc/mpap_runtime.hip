@@ -822,10 +822,9 @@ int search_shape(int stage_cap, int block_threads, int wave_min_targets, SearchS
             L.halves_forced = merge_halves > 0;
         }
     }
-    // by default a wave-per-target iteration needs four small targets per wave
     if (wave_min_targets < 0) L.wcap = 0;
-    L.wmin = wave_min_targets > 0 ? wave_min_targets : 4 * L.nblocks * (L.threads / 64);
     L.explicit_wmin = wave_min_targets > 0;
+    L.wmin = wave_min_targets > 0 ? wave_min_targets : 0;
     return MPAP_OK;
 }
 
@@ -871,11 +870,11 @@ SearchArgs search_args(const mpap_graph *g, Workspace *w, const SearchPrep &p,
     a.qgoff = g->qgoff; a.goal_list = g->goal_list; a.qearly = w->qearly; a.qstop = w->qstop;
     a.early_any = p.early_any ? 1 : 0;
     a.capB = L.capB; a.capC = L.capC; a.nblocks = L.nblocks;
-    a.wcap = L.wcap; a.wslice = L.wslice; a.wmin = L.wmin;
+    a.wcap = L.wcap; a.wslice = L.wslice; a.wmin = wave_min(L); a.wlight = kWaveChildren;
     a.halves = L.halves; a.half_lds = L.half_lds; a.capBh = L.capBh; a.capCh = L.capCh;
     a.big_front = L.big_front; a.big_children = L.big_children; a.halves_min = L.halves_min;
     a.pool = w->pool; a.pool_cap = w->pool_cap; a.pool_top = w->pool_top; a.nb = w->nb;
-    a.minopen = w->minopen; a.gcnt = w->gcnt; a.fo = w->fo; a.mark = w->mark; a.wt = w->wt;
+    a.minopen = w->minopen; a.gcnt = w->gcnt; a.fo = w->fo; a.wt = w->wt;
     a.alist = w->alist; a.acnt = w->acnt; a.mcur = w->mcur; a.claim = w->claim;
     a.queue_cap = (int)(L.lds / 4) - 2 * L.threads - 32; a.F = w->F; a.F_cap = w->F_cap;
     a.arena = w->arena; a.arena_cap = std::min<long long>(w->arena_cap, 0x7ffffff0ll);

@@ -153,7 +153,6 @@ extern "C" int mpap_search_noalloc(const mpap_graph *gc, const mpap_search_param
     w.fo = cv.take<int4>(n);
     w.minopen = cv.take<float>(n);
     w.gcnt = cv.take<int>(n);
-    w.mark = cv.take<int>(n);
     w.wt = cv.take<int>(n);
     w.alist = cv.take<int>((size_t)kListRegions * n);
     w.acnt = cv.take<int>(2 * kListRegions);

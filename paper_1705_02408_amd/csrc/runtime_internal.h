@@ -167,7 +167,6 @@ struct Workspace {
     float *minopen = nullptr;
     int *gcnt = nullptr;
     int4 *fo = nullptr;
-    int *mark = nullptr;
     int *wt = nullptr;
     int *alist = nullptr;
     int *acnt = nullptr;
@@ -209,7 +208,7 @@ struct Workspace {
 
     void free_all() {
         dfree(pool); dfree(pool_top); dfree(nb); dfree(minopen); dfree(gcnt); dfree(fo);
-        dfree(mark); dfree(wt); dfree(alist); dfree(acnt); dfree(mcur); dfree(claim); dfree(F); dfree(arena); dfree(part_cnt);
+        dfree(wt); dfree(alist); dfree(acnt); dfree(mcur); dfree(claim); dfree(F); dfree(arena); dfree(part_cnt);
         dfree(part_open); dfree(part_step); dfree(bar); dfree(err); dfree(out); dfree(wstat);
         dfree(spill); dfree(spill_flags);
         dfree(g_out); dfree(g_out_node); dfree(g_n); dfree(g_count); dfree(g_total);
@@ -249,7 +248,6 @@ inline int ws_alloc_nodes(Workspace *w, int32_t n, int nblocks) {
     if ((r = dalloc(&w->minopen, n))) return r;
     if ((r = dalloc(&w->gcnt, n))) return r;
     if ((r = dalloc(&w->fo, n))) return r;
-    if ((r = dalloc(&w->mark, n))) return r;
     if ((r = dalloc(&w->wt, n))) return r;
     if ((r = dalloc(&w->alist, (size_t)kListRegions * n))) return r;
     if ((r = dalloc(&w->acnt, 2 * kListRegions))) return r;
@@ -398,7 +396,7 @@ struct SearchPrep {
 struct SearchShape {
     int threads = 1024, capC = 1024, capB = 0, nblocks = 0;
     int wcap = 0, wslice = 0;  // single-wave merges: front capacity, LDS slice bytes
-    int wmin = 0;              // and the least small-target count that uses them
+    int wmin = 0;              // and the least target count that uses them (see wave_min)
     bool explicit_wmin = false;
     // merges by halves (1024-thread workgroups, workgroup-only build): each
     // half's LDS bytes, front stage and chunk; fronts above big_front labels
@@ -431,15 +429,25 @@ int search_goal_finish(mpap_graph *g, const SearchPrep &p, const SearchShape &L,
 int acquire_workspace(mpap_graph *g, const SearchShape &L, Workspace **out);
 GoalArgs goal_args(const mpap_graph *g, Workspace *w);
 // The search kernel build for a launch on g: with single-wave merges only
-// when some iteration can have wmin targets (or the caller asked for them).
-// The build with merges by halves runs on roadmaps of at least 16 nodes per
-// workgroup (smaller ones rarely have iterations with enough targets), or
-// when the caller asked for it.
+// when some iteration can have wave_min targets (or the caller asked for
+// them), with merges by halves on roadmaps of at least 16 nodes per workgroup
+// (smaller ones rarely have iterations with enough targets), or when the
+// caller asked for it.
 inline bool halves_build(const SearchShape &L, int n) {
     return L.halves && (L.halves_forced || n >= 16 * (long long)L.nblocks);
 }
+// The least targets of an iteration that merges by single waves: four waves a
+// target for two objectives (a lane's test of a child is one binary search;
+// 6D roadmap of 20,000 states 7.4, 7.6, 8.0, 8.3 ms at 512, 1,024, 2,048 and
+// 4,096, against 11.9 by halves; 2D of 5,000 samples, whose fronts are long,
+// 9.5, 8.9, 8.9, 8.8 against 8.6), a quarter of one for three, whose children
+// scan prefixes of the front (3D of 20,000 samples 19.5 ms against 12.4).
+inline int wave_min(const SearchShape &L) {
+    const int waves = L.nblocks * (L.threads / 64);
+    return L.explicit_wmin ? L.wmin : L.obj == 2 && !L.halves_forced ? waves / 4 : 4 * waves;
+}
 inline bool wave_build(const SearchShape &L, int n) {
-    return L.wcap > 0 && (L.explicit_wmin || n >= 4 * (long long)L.wmin);
+    return L.wcap > 0 && (L.explicit_wmin || n >= 4 * (long long)wave_min(L));
 }
 // The search build for a launch on g (see search_kernels.h).
 inline const void *search_kernel_for(const SearchShape &L, int n) {

@@ -22,6 +22,10 @@ constexpr int kErrTarget = 8;   // a queued merge target is not a node (internal
 // from kWeightClassBase * 2^(c-1) on, the last class open-ended.  Heavier
 // classes are merged first, so the longest merges of an iteration start early.
 constexpr int kWeightClasses = 10;
+// Most children of a target that one wave merges; above, a whole workgroup
+// (32 planar and spatial queries at once: 25.7 ms at 32, 22.9 at 64, 21.8 at
+// 128, 23.4 at 256; a spatial roadmap of 20,000 samples 6.3, 5.7, 5.1, 4.7 ms).
+constexpr int kWaveChildren = 128;
 constexpr int kWeightClassBase = 128;
 // Target list regions of n entries each: all targets, one per weight class,
 // and (with merges by halves) two of targets the whole workgroup merges: the
@@ -103,21 +107,21 @@ struct SearchArgs {
     float *minopen;    // per node least cost of an open label (+inf: none)
     int *gcnt;         // per node group size of the current iteration
     int4 *fo;          // per node {frontier offset, count, wave, first open label index}
-    int *mark;         // per node last wave it was queued as merge target (wave build)
-    int *wt;           // per node children queued to it this iteration (workgroup-only
-                       // build; zero between iterations)
+    int *wt;           // per node children queued to it this iteration (zero between
+                       // iterations)
     int *alist;        // merge targets of the current wave, kListRegions regions of n:
-                       // wave build: fronts of at most wcap labels in region 0 (merged
-                       // by one wave), larger ones in region 1; workgroup-only build:
-                       // every target in region 0, then by weight class c in region 1+c,
-                       // with merges by halves the whole workgroup's in regions
-                       // 1+kWeightClasses (heavy) and 2+kWeightClasses
+                       // every target in region 0, then by weight class c in region 1+c;
+                       // merged by single waves in region 1+kWeightClasses; with merges
+                       // by halves the whole workgroup's in regions 1+kWeightClasses
+                       // (heavy) and 2+kWeightClasses
     int *acnt;         // [2 kListRegions] target count of region r at [2 r + wave parity]
     int *mcur;         // [2 kListRegions] next target to merge, same layout
     int *claim;        // [2][kClaimWords] single-wave claims by wave parity
     int queue_cap;     // LDS words that select gathers new targets in
-    int wcap;          // largest front merged by a single wave (0: none)
-    int wmin;          // single-wave merges in iterations with at least wmin small targets
+    int wcap;          // front labels a wave's slice holds (0: no single-wave merges)
+    int wlight;        // most children of a target merged by a single wave (its front and
+                       // they have to fit the slice together)
+    int wmin;          // single-wave merges in iterations with at least wmin targets
     int wslice;        // LDS bytes of one wave's slice in single-wave merges
     // merges by halves (workgroup-only build, 1024-thread workgroups): each
     // half of a workgroup merges its own targets in its half of the LDS

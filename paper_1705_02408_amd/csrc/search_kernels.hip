@@ -138,7 +138,6 @@ __device__ __forceinline__ void phase_count(const SearchArgs &a, long long istep
 // of the per-node counts on top of the block's offset); each flagged node is
 // then handled by one wave: its group labels are copied to the frontier,
 // closed and given their arena ids, and its out-neighbours are queued.
-template <bool kSplit>
 __device__ __forceinline__ void phase_select(const SearchArgs &a, long long istep, int wave, long long abase,
                              long long myoff, int lo, int hi, int *list, int *list_off,
                              int *scan, int *queue, int queue_cap) {
@@ -147,20 +146,13 @@ __device__ __forceinline__ void phase_select(const SearchArgs &a, long long iste
     const int nw = blockDim.x >> 6;
     const unsigned wp = wave_par(wave);
     long long carry = myoff;
-    // New targets gather in LDS, a segment per wave (and list), and go out
-    // with one slot reservation per block and list at the end of the phase:
-    // one a wave of 64 out-edges had a thousand and more reservations an
-    // iteration wait for each other at 12 ns.  A full segment goes out alone.
-    const int cap = queue_cap / ((kSplit ? 2 : 1) * nw);
-    int *const seg0 = queue + w * cap, *const seg1 = queue + (nw + w) * cap;
-    int q0 = 0, q1 = 0;  // queued by this wave
-    auto flush = [&](const int *seg, int n, int counter, int region) {
-        int base = 0;
-        if (l == 0) base = atomicAdd(&a.acnt[counter + wp], n);
-        base = __shfl(base, 0, 64);
-        wsync();
-        for (int i = l; i < n; i += 64) a.alist[(size_t)region * a.n + base + i] = seg[i];
-    };
+    // New targets gather in LDS, a segment per wave, and go out with one slot
+    // reservation per block at the end of the phase: with one a wave of 64
+    // out-edges, a thousand and more reservations an iteration waited for
+    // each other at 12 ns.  A full segment goes out alone.
+    const int cap = queue_cap / nw;
+    int *const seg = queue + w * cap;
+    int queued = 0;  // by this wave
     for (int tb = lo; tb < hi; tb += blockDim.x) {
         const int v = tb + threadIdx.x;
         const int g = (v < hi) ? a.gcnt[v] : 0;
@@ -224,66 +216,49 @@ __device__ __forceinline__ void phase_select(const SearchArgs &a, long long iste
                 if (a.nq > 1) atomicMax(&a.qlast[query_of(a, vv)], wave);
                 else if (vv >= 0) a.qlast[0] = wave;
             }
-            // queue out-neighbours as merge targets of this wave, by the size
-            // of their front (one slot reservation per wave of 64 out-edges)
+            // queue out-neighbours as merge targets of this wave; the weight
+            // (children queued) starts at zero each iteration, and the first
+            // to add to it queues the target
             for (int e0 = eb; e0 < ee; e0 += 64) {
                 const int e = e0 + l;
                 int x = -1;
-                bool fresh = false, big = false;
+                bool fresh = false;
                 if (e < ee) {
                     x = e0 == eb ? x_first : a.ocol[e];
-                    if constexpr (kSplit) {
-                        fresh = atomicExch(&a.mark[x], wave) != wave;
-                        if (fresh) big = a.nb[x].z > a.wcap;
-                    } else {
-                        // the weight (children queued) starts at zero each iteration
-                        fresh = atomicAdd(&a.wt[x], max(run, 1)) == 0;
-                    }
+                    fresh = atomicAdd(&a.wt[x], max(run, 1)) == 0;
                 }
-                const uint64_t fs = ballot64(fresh && !big), fb = ballot64(fresh && big);
-                if (fs) {
-                    if (q0 + 64 > cap) {
-                        flush(seg0, q0, 0, 0);
-                        q0 = 0;
-                        wsync();
-                    }
-                    if (fresh && !big) seg0[q0 + lanes_below(fs)] = x;
-                    q0 += (int)__popcll(fs);
+                const uint64_t fs = ballot64(fresh);
+                if (fs == 0) continue;
+                if (queued + 64 > cap) {
+                    int base = 0;
+                    if (l == 0) base = atomicAdd(&a.acnt[wp], queued);
+                    base = __shfl(base, 0, 64);
+                    wsync();
+                    for (int q = l; q < queued; q += 64) a.alist[base + q] = seg[q];
+                    wsync();
+                    queued = 0;
                 }
-                if (kSplit && fb) {
-                    if (q1 + 64 > cap) {
-                        flush(seg1, q1, 2, 1);
-                        q1 = 0;
-                        wsync();
-                    }
-                    if (fresh && big) seg1[q1 + lanes_below(fb)] = x;
-                    q1 += (int)__popcll(fb);
-                }
+                if (fresh) seg[queued + lanes_below(fs)] = x;
+                queued += (int)__popcll(fs);
             }
         }
         carry += tot;
         __syncthreads();
     }
     // what is left, the block's waves behind each other
-#pragma unroll
-    for (int r = 0; r < (kSplit ? 2 : 1); ++r) {
-        const int q = r == 0 ? q0 : q1;
-        if (l == 0) scan[w] = q;
-        __syncthreads();
-        int before = 0, all = 0;
-        for (int i = 0; i < nw; ++i) {
-            if (i < w) before += scan[i];
-            all += scan[i];
-        }
-        __syncthreads();
-        if (all == 0) continue;  // (the same in every thread)
-        if (threadIdx.x == 0) scan[0] = atomicAdd(&a.acnt[2 * r + wp], all);
-        __syncthreads();
-        const int base = scan[0] + before;
-        const int *seg = r == 0 ? seg0 : seg1;
-        for (int i = l; i < q; i += 64) a.alist[(size_t)r * a.n + base + i] = seg[i];
-        __syncthreads();
+    if (l == 0) scan[w] = queued;
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int i = 0; i < nw; ++i) {
+        if (i < w) before += scan[i];
+        all += scan[i];
     }
+    __syncthreads();
+    if (all == 0) return;  // (the same in every thread)
+    if (threadIdx.x == 0) scan[0] = atomicAdd(&a.acnt[wp], all);
+    __syncthreads();
+    const int base = scan[0] + before;
+    for (int q = l; q < queued; q += 64) a.alist[base + q] = seg[q];
 }
 
 // ------------------------------------------------------------------ P3
@@ -1380,7 +1355,6 @@ __global__ void __launch_bounds__(256) k_search_init(SearchArgs a) {
         a.minopen[v] = MPAP_INF;
         a.gcnt[v] = 0;
         a.fo[v] = make_int4(0, 0, -1, 0);
-        a.mark[v] = -1;
         a.wt[v] = 0;
     }
     if (v == 0) {
@@ -1469,41 +1443,61 @@ __device__ __forceinline__ void carve_lds(unsigned char *lds, const SearchArgs &
 // Targets 0..n-1 of a list handed to the waves of the grid one at a time.
 // Claims at one counter wait for each other (12 ns each: 6 ms of a search
 // of 790,000 small merges), so the list is split in kClaimGroups ranges with
-// a counter each, in lines of their own; a block starts at its range and goes
-// on to the others once that is used up.  Whole waves call.
+// a counter each, in lines of their own; a block starts at its range, each of
+// its waves with a target by its place, and goes on to the others once that
+// is used up.  Whole waves call.
 struct WaveClaims {
     int *cur;  // counters, kBarLine words apart
-    int n, g;
-    bool home;  // its own range is not used up
-    __device__ __forceinline__ WaveClaims(int *cursors, int targets, int block)
-        : cur(cursors), n(targets), g(block % kClaimGroups), home(true) {}
+    int n, blocks, waves, g, place;
+    bool left;  // false: all are claimed
+    __device__ __forceinline__ WaveClaims(int *cursors, int targets, int block, int nblocks)
+        : cur(cursors), n(targets), blocks(nblocks), waves((int)blockDim.x >> 6),
+          g(block % kClaimGroups),
+          place(block / kClaimGroups * waves +
+                __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)),
+          left(true) {}
     __device__ __forceinline__ int first(int i) const {
         return (int)((long long)n * i / kClaimGroups);
     }
+    // targets of range i that go to waves by their places
+    __device__ __forceinline__ int placed(int i) const {
+        return (blocks - i + kClaimGroups - 1) / kClaimGroups * waves;
+    }
     // the next target, or -1 when all are claimed
     __device__ __forceinline__ int next() {
-        for (;;) {
-            if (home) {
-                int k = 0;
-                if (lane_id() == 0)
-                    k = __hip_atomic_fetch_add(cur + g * kBarLine, 1, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                k = first(g) + __shfl(k, 0, 64);
-                if (k < first(g + 1)) return k;
-            }
+        if (place >= 0) {
+            const int k = first(g) + place;
+            place = -1;
+            if (k < first(g + 1)) return k;
+        } else if (left) {
+            int k = 0;
+            if (lane_id() == 0)
+                k = __hip_atomic_fetch_add(cur + g * kBarLine, 1, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            k = first(g) + placed(g) + __builtin_amdgcn_readfirstlane(k);
+            if (k < first(g + 1)) return k;
+        }
+        while (left) {
             // the next range with targets left, if any (counters only grow)
             const int i = lane_id() % kClaimGroups;
             const int used = __hip_atomic_load(cur + i * kBarLine, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t left = ballot64(lane_id() < kClaimGroups && first(i) + used < first(i + 1));
-            if (left == 0) {
-                home = false;
-                return -1;
+            const uint64_t some = ballot64(lane_id() < kClaimGroups &&
+                                           first(i) + placed(i) + used < first(i + 1));
+            if (some == 0) {
+                left = false;
+                break;
             }
-            const uint64_t after = left & ~((2ull << g) - 1ull);
-            g = (int)__ffsll((unsigned long long)(after ? after : left)) - 1;
-            home = true;
+            const uint64_t after = some & ~((2ull << g) - 1ull);
+            g = (int)__ffsll((unsigned long long)(after ? after : some)) - 1;
+            int k = 0;
+            if (lane_id() == 0)
+                k = __hip_atomic_fetch_add(cur + g * kBarLine, 1, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            k = first(g) + placed(g) + __builtin_amdgcn_readfirstlane(k);
+            if (k < first(g + 1)) return k;
         }
+        return -1;
     }
 };
 
@@ -1523,6 +1517,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
     // the next whole-workgroup command}
     __shared__ int hbar[2][8];
     __shared__ int hctl[8];
+    __shared__ int cnt[kListRegions];  // this iteration's region counts
 
     const int G = (int)gridDim.x;
     const int b = (int)blockIdx.x;
@@ -1548,7 +1543,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
         long long* tr = (wave < a.wstat_cap) ? a.wstat + (size_t)wave * kTraceWords : nullptr;
         if (tr0 && tr) tr[kTrStart] = (long long)wall_clock64();
         if (threadIdx.x == 0 && b == 0) {
-            for (int r = 0; r < (kWaveMerges ? 2 : kListRegions); ++r) {
+            for (int r = 0; r < kListRegions; ++r) {
                 a.acnt[2 * r + wave_par(wave)] = 0;
                 a.mcur[2 * r + wave_par(wave)] = 0;
             }
@@ -1628,7 +1623,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
             // (its own view of the LDS: two node lists, scan words, the queue)
             int *const list = reinterpret_cast<int *>(lds);
             int *const scan = list + 2 * blockDim.x;
-            phase_select<kWaveMerges>(a, i_step, wave, abase, before, lo, hi, list,
+            phase_select(a, i_step, wave, abase, before, lo, hi, list,
                                       list + blockDim.x, scan, scan + 32, a.queue_cap);
         }
         if (tr0 && tr) tr[kTrSelectDone] = (long long)wall_clock64();
@@ -1641,36 +1636,13 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
         const unsigned wp = wave_par(wave);
         const int na = __hip_atomic_load(&a.acnt[wp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const long long m0 = (long long)wall_clock64();
-        // many small targets: one wave each; few: the workgroups share them
-        // (a single wave is slower per merge, so it pays only when the waves
-        // of the grid all have several targets)
-        const bool by_wave = kWaveMerges && a.wcap > 0 && na >= a.wmin;
-        if (by_wave) {
-            // small fronts: each wave takes targets itself and merges them in
-            // its LDS slice; fronts that outgrow it join the large list
-            WaveLds W;
-            carve_wave(lds, a, W);
-            WaveClaims claims(a.claim + wp * kClaimWords, na, b);
-            int k = claims.next();
-            while (k >= 0) {
-                const int x = a.alist[k];
-                const int k2 = claims.next();  // claimed while this one merges
-                if ((unsigned)x >= (unsigned)a.n) {
-                    if (lane_id() == 0) atomicOr(a.err, kErrTarget);
-                } else if (wave_merge_node<kObj>(a, x, wave, W, wv_cand)) {
-                    ++wv_merges;
-                } else if (lane_id() == 0) {
-                    const int kb = atomicAdd(&a.acnt[2 + wp], 1);
-                    a.alist[a.n + kb] = x;
-                }
-                k = k2;
-            }
-            __syncthreads();  // the slices are the workgroup's LDS again
-            grid_barrier(a.bar, G, epoch, a.err, kErrTimeout, kSpinLimit);
-        }
+        // no more targets than workgroups: each takes one, in any order
+        const bool plain = na <= G;
+        // single-wave merges of the light targets in this iteration
+        const bool by_wave = kWaveMerges && a.wcap > 0 && na >= a.wmin && !plain;
         // merges by halves in this iteration: enough targets for two per workgroup
-        const bool halves = kHalves && na >= a.halves_min;
-        if constexpr (!kWaveMerges) {
+        const bool halves = kHalves && na >= a.halves_min && !plain;
+        if (!plain) {
             // weight classes: every target once, by the children queued to it
             // (final after the select barrier; cleared here for the next
             // iteration), appended to its class region (one reservation per
@@ -1692,57 +1664,58 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                             if (wx > 4 * a.big_children || fz > a.capBh) c = kWeightClasses;
                             else if (wx > a.big_children || fz > a.big_front) c = kWeightClasses + 1;
                         }
+                        // light: the front and all its children fit a wave's slice
+                        if (by_wave && wx <= a.wlight && a.nb[x].z + wx <= a.wcap) c = kWeightClasses;
                         a.wt[x] = 0;
                     } else {
                         atomicOr(a.err, kErrTarget);
                     }
                 }
-                uint64_t todo = ballot64(c >= 0);
+                // (the first lane of each class reserves: one round trip)
+                uint64_t todo = ballot64(c >= 0), mine = 0;
                 while (todo) {
                     const int lead = (int)__ffsll((unsigned long long)todo) - 1;
                     const int cl = __shfl(c, lead, 64);
                     const uint64_t same = ballot64(c == cl);
-                    int base = 0;
-                    if (l == lead) base = atomicAdd(&a.acnt[2 * (1 + cl) + wp], (int)__popcll(same));
-                    base = __shfl(base, lead, 64);
-                    if (c == cl) a.alist[(1 + cl) * a.n + base + lanes_below(same)] = x;
+                    if (c == cl) mine = same;
                     todo &= ~same;
                 }
+                const int lead = mine ? (int)__ffsll((unsigned long long)mine) - 1 : l;
+                int base = 0;
+                if (mine && l == lead) base = atomicAdd(&a.acnt[2 * (1 + c) + wp], (int)__popcll(mine));
+                base = __shfl(base, lead, 64);
+                if (mine) a.alist[(size_t)(1 + c) * a.n + base + lanes_below(mine)] = x;
             }
             grid_barrier(a.bar, G, epoch, a.err, kErrTimeout, kSpinLimit);
         }
+        if (threadIdx.x < kListRegions)
+            cnt[threadIdx.x] = plain ? 0
+                                     : __hip_atomic_load(&a.acnt[2 * threadIdx.x + wp], __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x < 8) hctl[threadIdx.x] = threadIdx.x == 0 ? 0 : -1;
+        __syncthreads();
         // one workgroup per target, taken dynamically (merges differ widely in
-        // cost); the next one is claimed while the current one merges.  Wave
-        // build: the large fronts (and the small ones when no wave took them);
-        // workgroup-only build: the heaviest weight class first (with merges
-        // by halves: the whole workgroup's region first, then the classes by
-        // halves)
-        int nbig = 0, nsmall = na;
-        if constexpr (kWaveMerges) {
-            nbig = __hip_atomic_load(&a.acnt[2 + wp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (by_wave) nsmall = 0;
-        }
-        int *const cursor = &a.mcur[kWaveMerges ? 2 + wp : wp];
+        // cost): its own index first, then claims (256 first claims at one
+        // counter took 3 us); the next one is claimed while the current one
+        // merges; the heaviest weight class first (with merges by halves: the
+        // whole workgroup's region first, then the classes by halves; with
+        // single-wave merges the light targets last, a wave each)
+        const int nlight = by_wave ? cnt[1 + kWeightClasses] : 0;
+        const int nheavy = na - nlight;
+        int *const cursor = &a.mcur[wp];
         // thread 0's walk over the class regions (claims only grow); with
         // merges by halves each half's first thread walks on its own
-        int cls = kWeightClasses - 1, cbase = 0, ccnt = 0;
-        if (!kWaveMerges && (threadIdx.x & (halves ? 511 : 1023)) == 0)
-            ccnt = __hip_atomic_load(&a.acnt[2 * (1 + cls) + wp], __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
+        int cls = kWeightClasses, cbase = 0, ccnt = 0;
         // list index of the k-th claim, -1 when none is left
         auto locate = [&](int k) -> int {
-            if constexpr (kWaveMerges) {
-                return k;  // resolved below
-            } else {
-                if (k >= na) return -1;
-                while (cls > 0 && k >= cbase + ccnt) {
-                    cbase += ccnt;
-                    --cls;
-                    ccnt = __hip_atomic_load(&a.acnt[2 * (1 + cls) + wp], __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-                }
-                return k < cbase + ccnt ? (1 + cls) * a.n + (k - cbase) : -1;
+            if (k >= nheavy) return -1;
+            if (plain) return k;
+            while (cls > 0 && k >= cbase + ccnt) {
+                cbase += ccnt;
+                --cls;
+                ccnt = cnt[1 + cls];
             }
+            return k < cbase + ccnt ? (1 + cls) * a.n + (k - cbase) : -1;
         };
         // Whole-workgroup merges come from one loop (one call site per
         // build): thread 0 claims and hands out the next target, or -2 (run
@@ -1753,25 +1726,19 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
         // target, and the halves go on.
         // the whole workgroup's regions rb (heavy) and rb + 1 as one list
         const int rb = 1 + kWeightClasses;
-        const int nw0 = halves ? __hip_atomic_load(&a.acnt[2 * rb + wp], __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT)
-                               : 0;
-        const int nwhole = halves ? nw0 + __hip_atomic_load(&a.acnt[2 * (rb + 1) + wp],
-                                                            __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT)
-                                  : 0;
+        const int nw0 = halves ? cnt[rb] : 0;
+        const int nwhole = halves ? nw0 + cnt[rb + 1] : 0;
         int *const wcur = &a.mcur[2 * rb + wp];
         // thread 0: 0 whole-workgroup region, 1 after the halves, 2 no halves
         int phase = halves ? 0 : 2;
         int next = -1;
-        if (threadIdx.x == 0) next = phase == 0 ? atomicAdd(wcur, 1) : locate(atomicAdd(cursor, 1));
+        if (threadIdx.x == 0)
+            next = phase == 0 ? b : locate(b);
         // (the half and the wave index are uniform in a wave: read from the
         // first lane, so that the half's LDS views stay in scalar registers)
         // (merges by halves run in 1024-thread workgroups: halves of 512)
         const int h = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 9);
-        if (threadIdx.x < 8) hctl[threadIdx.x] = threadIdx.x == 0 ? 0 : -1;
-        __syncthreads();
-        for (;;) {
+        while (nheavy > 0) {
             if (threadIdx.x == 0) {
                 int cmd = -1;
                 for (;;) {
@@ -1784,7 +1751,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                         }
                         x = a.alist[(size_t)(next < nw0 ? rb : rb + 1) * a.n +
                                     (next < nw0 ? next : next - nw0)];
-                        next = atomicAdd(wcur, 1);
+                        next = G + atomicAdd(wcur, 1);
                     } else if (phase == 1) {
                         if (hctl[1] >= 0) {
                             x = hctl[1];
@@ -1801,12 +1768,12 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                         }
                     } else {
                         const int idx = next;
-                        if (kWaveMerges ? idx >= nsmall + nbig : idx < 0) break;
-                        next = locate(atomicAdd(cursor, 1));
-                        x = kWaveMerges ? (idx < nsmall ? a.alist[idx] : a.alist[a.n + (idx - nsmall)])
-                                        : a.alist[idx];
+                        if (idx < 0) break;
+                        next = plain ? -1 : locate(G + atomicAdd(cursor, 1));
+                        x = a.alist[idx];
                     }
                     if ((unsigned)x < (unsigned)a.n) {
+                        if (plain) a.wt[x] = 0;  // (the class pass clears it otherwise)
                         cmd = x;
                         break;
                     }
@@ -1840,14 +1807,17 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                 __syncthreads();
                 int hnext = -1;
                 if (gh.tid == 0) {
-                    hnext = hctl[3 + h] >= 0 ? hctl[3 + h] : locate(atomicAdd(cursor, 1));
-                    hctl[3 + h] = -1;
+                    // -1: the first claim (2 b + h), -2: none carried over
+                    hnext = hctl[3 + h] >= 0    ? hctl[3 + h]
+                            : hctl[3 + h] == -1 ? locate(2 * b + h)
+                                                : locate(2 * G + atomicAdd(cursor, 1));
+                    hctl[3 + h] = -2;
                 }
                 for (;;) {
                     if (gh.tid == 0) {
                         if (__hip_atomic_load(&hctl[0], __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_WORKGROUP) != 0) {
-                            hctl[3 + h] = hnext;  // claimed, not merged: carried over
+                            hctl[3 + h] = hnext >= 0 ? hnext : -2;  // claimed, not merged: carried over
                             hnext = -2;
                         }
                         if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
@@ -1859,7 +1829,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                     const int idx = sh.misc[2];
                     gsync(gh);
                     if (idx < 0) break;
-                    if (gh.tid == 0) hnext = locate(atomicAdd(cursor, 1));
+                    if (gh.tid == 0) hnext = locate(2 * G + atomicAdd(cursor, 1));
                     const int x = a.alist[idx];
                     long long cand = 0;
                     if ((unsigned)x >= (unsigned)a.n) {
@@ -1879,6 +1849,27 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                 __syncthreads();
             }
         }
+        if constexpr (kWaveMerges) {
+            if (by_wave) {
+                // (every wave has left the loop above: the LDS is the slices')
+                WaveLds W;
+                carve_wave(lds, a, W);
+                const int *const light = a.alist + (size_t)(1 + kWeightClasses) * a.n;
+                WaveClaims claims(a.claim + wp * kClaimWords, nlight, b, G);
+                int k = claims.next();
+                while (k >= 0) {
+                    const int x = light[k];
+                    const int k2 = claims.next();  // claimed while this one merges
+                    // (it fits the slice by its weight, so it cannot back out)
+                    if ((unsigned)x < (unsigned)a.n && wave_merge_node<kObj>(a, x, wave, W, wv_cand))
+                        ++wv_merges;
+                    else if (lane_id() == 0)
+                        atomicOr(a.err, kErrTarget);
+                    k = k2;
+                }
+                __syncthreads();
+            }
+        }
         if (threadIdx.x == 0 && tr) {
             const long long dm = (long long)wall_clock64() - m0;
             atomicMax((unsigned long long *)&tr[kTrMaxMerge], (unsigned long long)dm);
@@ -1887,7 +1878,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
         grid_barrier(a.bar, G, epoch, a.err, kErrTimeout, kSpinLimit);
         if (tr0 && tr) {
             tr[kTrMerged] = (long long)wall_clock64();
-            tr[kTrTargets] = na + nbig;
+            tr[kTrTargets] = na;
         }
 
         abase += total;

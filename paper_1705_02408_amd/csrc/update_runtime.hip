@@ -149,7 +149,7 @@ __global__ void k_mark_seeds(int n, const uint8_t *lost, const int *rptr, const 
 // Per node: the labels of a seed open again (meta = parent + 1 with the open
 // bit); node state for the next search (group bookkeeping cleared).
 __global__ void k_reopen(int n, int4 *nb, float4 *pool, const int2 *arena, const uint8_t *seed,
-                         float *minopen, int4 *fo, int *gcnt, int *mark, int *wt) {
+                         float *minopen, int4 *fo, int *gcnt, int *wt) {
     const int l = threadIdx.x & 63;
     const int v = (int)(((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     if (v >= n) return;
@@ -167,7 +167,6 @@ __global__ void k_reopen(int n, int4 *nb, float4 *pool, const int2 *arena, const
         minopen[v] = s ? pool[(size_t)(unsigned)b.x].x : MPAP_INF;
         fo[v] = make_int4(0, 0, -1, s ? 0 : b.z);
         gcnt[v] = 0;
-        mark[v] = -1;
         wt[v] = 0;
     }
 }
@@ -425,7 +424,7 @@ int mpap_search_update(const mpap_result *prev, const mpap_graph *gc,
         k_seed_tails<<<div_up(n, 256), 256, 0, s>>>(n, ndirty, seed);
         k_mark_seeds<<<div_up(n, 256), 256, 0, s>>>(n, lost, g->rptr, g->rsrc, seed);
         k_reopen<<<div_up(64ll * n, 256), 256, 0, s>>>(n, w->nb, w->pool, w->arena, seed,
-                                                       w->minopen, w->fo, w->gcnt, w->mark,
+                                                       w->minopen, w->fo, w->gcnt,
                                                        w->wt);
         k_update_words<<<1, 256, 0, s>>>(a);
         HIP_TRY(hipGetLastError());

@@ -545,6 +545,35 @@ def test_hub_with_many_in_edge_tiles(n_obj, threads, lam, halves):
     dg.close()
 
 
+@pytest.mark.parametrize("n_obj", [2, 3])
+def test_single_wave_and_workgroup_merges_in_one_iteration(n_obj):
+    """Spokes with a few children each go to single waves, the hub (thousands)
+    and, with a slice of 64 labels, the layers before it to workgroups, in the
+    same iterations."""
+    g, hub = hub_graph(11)
+    ref = osearch.search(g, 0.5, n_obj)
+    for stage in (0, 64):
+        dg, res = run(g, 0.5, n_obj, radius=0.5, lam=2.0, wave_min_targets=1, stage_cap=stage)
+        assert res.stats()["wave_build"] == 1
+        check_against_oracle(g, res, ref, 0.5, n_obj)
+        res.close()
+        dg.close()
+
+
+@pytest.mark.parametrize("n_obj,wave", [(2, 1), (3, 0)])
+def test_default_build_by_objectives(n_obj, wave):
+    """From 4,096 nodes on, two-objective searches merge by single waves where
+    an iteration has enough targets; three-objective ones don't."""
+    env = synth.plain3d(8, n=4500)
+    g = ograph.build_graph(env)
+    ref = osearch.search(g, env.beta, n_obj)
+    dg, res = run(g, env.beta, n_obj, radius=env.radius, lam=2.0)
+    assert res.stats()["wave_build"] == wave
+    check_against_oracle(g, res, ref, env.beta, n_obj, all_nodes=False, node_stride=3)
+    res.close()
+    dg.close()
+
+
 @pytest.mark.parametrize("threads,wmin", [(256, -1), (512, -1), (1024, -1), (1024, 1)])
 def test_node_with_many_out_edges(threads, wmin):
     """A row of 12,000 out-edges: the new targets of one wave outgrow its part
