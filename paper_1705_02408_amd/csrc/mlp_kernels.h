@@ -16,34 +16,33 @@ constexpr int kOffB2 = kOffW2 + kMlpH * kMlpH;
 constexpr int kOffW3 = kOffB2 + kMlpH;
 constexpr int kOffB3 = kOffW3 + kMlpH;
 constexpr int kMlpParams = kOffB3 + 1;  // 5313
-// bfloat16 copies: W1[16][64], W2[64][64], w3[64]
+// bfloat16 copies: the operands of both layers' products in the lanes' order
+// (a lane's eight values side by side: one 16-byte load each instead of eight
+// strided ones), W2[64][64] in natural order for the way back, w3[64]
 constexpr int kBfW1 = 0;
 constexpr int kBfW2 = kBfW1 + kMlpIn * kMlpH;
-constexpr int kBfW3 = kBfW2 + kMlpH * kMlpH;
+constexpr int kBfW2F = kBfW2 + kMlpH * kMlpH;
+constexpr int kBfW3 = kBfW2F + kMlpH * kMlpH;
 constexpr int kMlpBf = kBfW3 + kMlpH;
-// partial sums written by one training wave (gradient of every parameter)
-constexpr int kGradWords = kMlpParams;
+// a block's partial gradient: every parameter, rounded up to 256 bytes
+constexpr int kGradWords = (kMlpParams + 63) / 64 * 64;
+// rows of a batch that a training workgroup takes at a time, 32 a wave
+constexpr int kTrainRows = 128;
+constexpr int kTrainBlocks = 64;  // most workgroups (and partial gradients)
 
 struct MlpDev {
     const float *p;        // float32 masters [kMlpParams]
     const uint16_t *pb;    // bfloat16 copies [kMlpBf]
 };
 
-// Training scratch for one batch of B rows.
+// One training batch of B rows.
 struct MlpTrain {
     const uint16_t *X;      // features of the training set [n][16] (bf16 bits)
     const float *t;         // targets [n]
     const long long *idx;   // batch rows (indices into X / t), [B]
     int B;                  // batch size, a multiple of 32
-    uint16_t *XT;           // [16][B] batch features, transposed
-    uint16_t *H1T;          // [64][B] bf16(relu(z1)), transposed
-    uint64_t *mask1;        // [B] bit h: z1[h] > 0
-    uint16_t *dZ2;          // [B][64] bf16(dL/dz2)
-    uint16_t *dZ2T;         // [64][B]
-    uint16_t *dZ1T;         // [64][B] bf16(dL/dz1)
     float *y;               // [B] outputs
-    float *part;            // [nparts][kGradWords] per-wave gradient partial sums
-    int nparts;
+    float *part;            // [blocks][kGradWords] per-block gradient partial sums
 };
 
 struct MlpAdam {
@@ -66,8 +65,9 @@ constexpr float kResidualScale = 256.0f;
 // drift = len * clamp(base + y / kResidualScale, 0, 1) (nullable; base nullable = 0)
 __global__ void k_mlp_infer(MlpDev d, const uint16_t *X, long long n, const float *len,
                             const float *base, float *y, float *drift);
-__global__ void k_mlp_train_fwd(MlpDev d, MlpTrain t);
-__global__ void k_mlp_train_bwd_h(MlpDev d, MlpTrain t);
-__global__ void k_mlp_train_bwd_w(MlpDev d, MlpTrain t);
+// *acc += sum over i < n of (network(X[idx[i]]) - t[idx[i]])^2
+__global__ void k_mlp_loss(MlpDev d, const uint16_t *X, const float *t, const long long *idx,
+                           long long n, float *acc);
+__global__ void k_mlp_train(MlpDev d, MlpTrain t);
 __global__ void k_mlp_adam(MlpAdam a);
 __global__ void k_mlp_to_bf16(const float *p, uint16_t *pb);

@@ -20,8 +20,6 @@ struct mpap_surrogate {
     int step = 0;
     // training scratch (grown on demand)
     int B = 0, nparts = 0;
-    uint16_t *XT = nullptr, *H1T = nullptr, *dZ2 = nullptr, *dZ2T = nullptr, *dZ1T = nullptr;
-    uint64_t *mask1 = nullptr;
     float *y = nullptr, *part = nullptr, *grad = nullptr;
     long long *idx = nullptr;
     long long idx_cap = 0;
@@ -33,22 +31,18 @@ struct mpap_surrogate {
 namespace {
 
 void sur_free_scratch(mpap_surrogate *s) {
-    dfree(s->XT); dfree(s->H1T); dfree(s->dZ2); dfree(s->dZ2T); dfree(s->dZ1T);
-    dfree(s->mask1); dfree(s->y); dfree(s->part); dfree(s->grad);
+    dfree(s->y); dfree(s->part); dfree(s->grad);
     s->B = 0;
 }
 
-// batch sizes are powers of two >= 64; nparts waves each sum B/nparts rows
+// batch sizes are powers of two >= 64; nparts workgroups share the rows
 int sur_scratch(mpap_surrogate *s, int B) {
     if (B < 64 || (B & (B - 1))) return fail(MPAP_ERR_INVAL, "batch must be a power of two >= 64");
     if (B == s->B) return MPAP_OK;
     sur_free_scratch(s);
-    const int nparts = std::min(64, B / 64);
+    const int nparts = std::min(kTrainBlocks, div_up(B, kTrainRows));
     int r;
-    if ((r = dalloc(&s->XT, (size_t)kMlpIn * B)) || (r = dalloc(&s->H1T, (size_t)kMlpH * B)) ||
-        (r = dalloc(&s->dZ2, (size_t)kMlpH * B)) || (r = dalloc(&s->dZ2T, (size_t)kMlpH * B)) ||
-        (r = dalloc(&s->dZ1T, (size_t)kMlpH * B)) || (r = dalloc(&s->mask1, B)) ||
-        (r = dalloc(&s->y, B)) || (r = dalloc(&s->part, (size_t)nparts * kGradWords)) ||
+    if ((r = dalloc(&s->y, B)) || (r = dalloc(&s->part, (size_t)nparts * kGradWords)) ||
         (r = dalloc(&s->grad, kMlpParams)))
         return r;
     s->B = B;
@@ -66,8 +60,7 @@ MlpDev dev_view(const mpap_surrogate *s) {
 MlpTrain train_view(mpap_surrogate *s, const uint16_t *X, const float *t, const long long *idx) {
     MlpTrain tr{};
     tr.X = X; tr.t = t; tr.idx = idx; tr.B = s->B;
-    tr.XT = s->XT; tr.H1T = s->H1T; tr.mask1 = s->mask1; tr.dZ2 = s->dZ2; tr.dZ2T = s->dZ2T;
-    tr.dZ1T = s->dZ1T; tr.y = s->y; tr.part = s->part; tr.nparts = s->nparts;
+    tr.y = s->y; tr.part = s->part;
     return tr;
 }
 
@@ -76,11 +69,7 @@ int sur_batch(mpap_surrogate *s, const uint16_t *X, const float *t, const long l
               float lr, bool apply, float *grad_out, hipStream_t st) {
     const MlpDev d = dev_view(s);
     const MlpTrain tr = train_view(s, X, t, idx);
-    const int blocks = s->nparts / 4 > 0 ? s->nparts / 4 : 1;
-    const int threads = (s->nparts >= 4 ? 4 : s->nparts) * 64;
-    k_mlp_train_fwd<<<blocks, threads, 0, st>>>(d, tr);
-    k_mlp_train_bwd_h<<<blocks, threads, 0, st>>>(d, tr);
-    k_mlp_train_bwd_w<<<blocks, threads, 0, st>>>(d, tr);
+    k_mlp_train<<<s->nparts, 256, 0, st>>>(d, tr);
     MlpAdam ad{};
     ad.p = s->p; ad.pb = s->pb; ad.m = s->m; ad.v = s->v; ad.part = s->part;
     ad.nparts = s->nparts; ad.lr = lr; ad.beta1 = 0.9f; ad.beta2 = 0.999f; ad.eps = 1e-8f;
@@ -90,23 +79,9 @@ int sur_batch(mpap_surrogate *s, const uint16_t *X, const float *t, const long l
         ad.c1 = (float)(1.0 - std::pow(0.9, (double)s->step));
         ad.c2 = (float)(1.0 - std::pow(0.999, (double)s->step));
     }
-    k_mlp_adam<<<div_up(kMlpParams, 256), 256, 0, st>>>(ad);
+    k_mlp_adam<<<div_up(kMlpParams, 64), 512, 0, st>>>(ad);
     HIP_TRY(hipGetLastError());
     return MPAP_OK;
-}
-
-// acc += sum over i < n of (y[idx[i]] - t[idx[i]])^2
-__global__ void k_sq_err(const float *y, const float *t, const long long *idx, long long n,
-                         float *acc) {
-    float s = 0.f;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long k = idx[i];
-        const float d = y[k] - t[k];
-        s += d * d;
-    }
-    s = wave_sum(s);
-    if (lane_id() == 0) atomicAdd(acc, s);
 }
 
 __global__ void k_zero_f32(float *p, int n) {
@@ -203,7 +178,7 @@ int mpap_surrogate_create(mpap_surrogate **out) {
     HIP_TRY(hipMemcpy(s->p, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(s->m, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(s->v, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice));
-    k_mlp_to_bf16<<<div_up(kMlpH * kMlpH, 256), 256>>>(s->p, s->pb);
+    k_mlp_to_bf16<<<div_up(kMlpParams, 256), 256>>>(s->p, s->pb);
     HIP_TRY(hipDeviceSynchronize());
     *out = s;
     return MPAP_OK;
@@ -227,7 +202,7 @@ int mpap_surrogate_set_params(mpap_surrogate *s, const float *params, int32_t co
     HIP_TRY(hipMemcpy(s->m, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(s->v, z.data(), sizeof(float) * kMlpParams, hipMemcpyHostToDevice));
     s->step = 0;
-    k_mlp_to_bf16<<<div_up(kMlpH * kMlpH, 256), 256>>>(s->p, s->pb);
+    k_mlp_to_bf16<<<div_up(kMlpParams, 256), 256>>>(s->p, s->pb);
     HIP_TRY(hipDeviceSynchronize());
     return MPAP_OK;
 }
@@ -400,19 +375,14 @@ int mpap_surrogate_train(mpap_surrogate *s, const mpap_graph *gc, const int64_t 
         }
         if (epoch_loss) {
             // mean squared error of the updated network over the training edges
-            float *yall = nullptr;
-            if ((r = dalloc(&yall, g->e))) return r;
-            const int blocks = std::max(1, std::min(div_up(g->e, 128), 2048));
-            k_mlp_infer<<<blocks, 256, 0, st>>>(dev_view(s), g->feat, g->e, nullptr, nullptr,
-                                                yall, nullptr);
+            // (one atomic a workgroup: few of them)
             k_zero_f32<<<1, 64, 0, st>>>(s->sq, 1);
-            k_sq_err<<<std::max(1, std::min(div_up(n_train, 256), 1024)), 256, 0, st>>>(
-                yall, s->t_all, s->idx, n_train, s->sq);
+            k_mlp_loss<<<std::max(1, std::min(div_up(n_train, 128), 256)), 256, 0, st>>>(
+                dev_view(s), g->feat, s->t_all, s->idx, n_train, s->sq);
             float sum = 0.f;
             HIP_TRY(hipMemcpyAsync(&sum, s->sq, sizeof(float), hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
             epoch_loss[ep] = sum / (float)n_train;
-            dfree(yall);
         }
     }
     HIP_TRY(hipStreamSynchronize(st));

@@ -80,6 +80,31 @@ def test_gradient_matches_reference(n):
     s.close()
 
 
+@pytest.mark.parametrize("n", [128, 8192, 16384])
+def test_gradient_by_row_groups(n):
+    """One row group, as many as there are workgroups, and two each (64 rows,
+    half a group, and 4,096 are above), within the same bound."""
+    test_gradient_matches_reference(n)
+
+
+def test_epoch_loss_on_a_ragged_edge_set(road3d):
+    """The loss after an epoch is the mean over all training edges (a count
+    that is no multiple of 32) of the network's squared error.  Each term is
+    the device's own output minus the same float32 target, so only the order
+    of n float32 additions differs: n 2^-24 relative."""
+    _, dg = road3d
+    n = 2048 + 77
+    edges = np.random.default_rng(6).permutation(dg.info()["e"])[:n]
+    s = mpap.Surrogate(seed=9)
+    loss = s.train(dg, edges, epochs=1, batch=1024, lr=1e-3)
+    X, base = mpap.mpap_edge_features(dg, with_base=True)
+    t = np.float32(256.0) * (mpap.mpap_graph_drift(dg, 0) / dg.export()["cost"] - base)
+    err = (s.forward(X[edges]) - t[edges]).astype(np.float64)
+    ref = float(np.mean(err * err))
+    assert abs(float(loss[0]) - ref) <= (n * 2.0 ** -24 + 4e-7) * ref, (loss[0], ref)
+    s.close()
+
+
 @pytest.fixture(scope="module")
 def road3d():
     env = synth.plain3d(0, n=3000)
