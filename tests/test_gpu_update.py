@@ -159,6 +159,42 @@ def test_update_after_edge_changes_equals_the_oracle(seed, n_obj, ints, lam):
     r0.close()
 
 
+@pytest.mark.parametrize("wide", [63, 64, 65, 130])
+def test_update_of_long_rows_and_deep_plans(wide):
+    """A row around and beyond 64 edges, some of them changed, swapped and
+    doubled (two parallel edges, one of which goes), before a chain of 300
+    nodes, one of whose edges gets dearer: plans with hundreds of ancestors."""
+    rng = np.random.default_rng(wide)
+    edges = [(0, 1 + i, float(rng.uniform(0.1, 1.0)), float(rng.uniform(0.0, 0.1)))
+             for i in range(wide)]
+    edges += [(1 + i, wide + 1, float(rng.uniform(0.1, 1.0)), float(rng.uniform(0.0, 0.1)))
+              for i in range(wide)]
+    edges += [(wide + 1 + k, wide + 2 + k, 0.25, 0.0005) for k in range(300)]
+    edges.append((0, wide, 0.0625, 0.09))
+    n = wide + 302
+    goal = np.zeros(n, dtype=np.uint8)
+    goal[-1] = 1
+    reset = np.zeros(n, dtype=np.uint8)
+    g0 = from_edges(n, edges, reset, goal)
+    new = [list(e) for e in edges]
+    for i in (0, 61, 62, wide - 2):
+        new[i][2] = new[i][2] * 1.5
+    new[2][2], new[3][2] = new[3][2], new[2][2]
+    new[2 * wide + 150][2] = 0.5
+    g1 = from_edges(n, [tuple(e) for e in new[:-1]], reset, goal)
+    d0, d1 = upload(g0), upload(g1)
+    for n_obj in (2, 3):
+        r0 = mpap.mpap_search(d0, 0.9, n_obj, 1.0, 0.5)
+        upd = mpap.mpap_search_update(r0, d1, 0.9, n_obj, 1.0, 0.5)
+        ref = osearch.search(g1, 0.9, n_obj)
+        for v in range(n):
+            assert front_digest(upd.node_front(v)) == front_digest(ref.node_front(v)), v
+        upd.close()
+        r0.close()
+    for d in (d0, d1):
+        d.close()
+
+
 def test_update_full_size_3d():
     """The 20,000-sample 3D workload (three objectives) after five obstacles
     are found: the update equals a fresh search."""
