@@ -560,6 +560,29 @@ def test_single_wave_and_workgroup_merges_in_one_iteration(n_obj):
         dg.close()
 
 
+@pytest.mark.parametrize("threads,stage_cap,n_obj,goals", [
+    (1024, 0, 3, 1499), (256, 0, 2, 1499), (256, 64, 3, 600), (1024, 0, 2, 1024), (512, 0, 3, 1)])
+def test_goal_front_over_many_goal_nodes(threads, stage_cap, n_obj, goals):
+    """Goal nodes by the hundred (more than a workgroup's threads, exactly as
+    many, one), on integer costs, so that equal vectors stand at several: the
+    oracle's front, each vector at the smallest goal node that has it."""
+    g = synth.tiny_random_graph(21, n=1500, p_reset=0.1, mean_degree=3.0, integer_costs=True)
+    mask = np.zeros(1500, dtype=np.uint8)
+    mask[1500 - goals:] = 1
+    g = dict(g, goal=mask)
+    ref = osearch.search(g, 1.0, n_obj)
+    dg, res = run(g, 1.0, n_obj, radius=1.0, lam=2.0, block_threads=threads, stage_cap=stage_cap)
+    check_against_oracle(g, res, ref, 1.0, n_obj, all_nodes=False, node_stride=5)
+    first = {}
+    for v in np.flatnonzero(mask):
+        for row in bits(res.node_front(int(v))):
+            first.setdefault(tuple(row), int(v))
+    fr = res.goal_front()
+    assert fr.goal_node.tolist() == [first[tuple(row)] for row in bits(fr.vecs)]
+    res.close()
+    dg.close()
+
+
 @pytest.mark.parametrize("n_obj,wave", [(2, 1), (3, 0)])
 def test_default_build_by_objectives(n_obj, wave):
     """From 4,096 nodes on, two-objective searches merge by single waves where
