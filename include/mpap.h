@@ -164,9 +164,10 @@ typedef struct {
     int32_t wave_min_targets; /* tuning: an iteration with at least this many merge
                                  targets merges those of small front and few new
                                  children with a single wave each (16 merges per CU at
-                                 once); 0 = a quarter of the waves of the grid when all
-                                 queries have two objectives, else four times them;
-                                 < 0 = never.  Never changes the result. */
+                                 once); 0 = any iteration with more targets than
+                                 workgroups when all queries have two objectives, else
+                                 four times the waves of the grid; < 0 = never.  Never
+                                 changes the result. */
     int32_t skip;             /* 1: leave this query out of a batched search (its root
                                  label is not seeded; its goal front is empty); 0 =
                                  search it */

@@ -795,7 +795,7 @@ int search_shape(int stage_cap, int block_threads, int wave_min_targets, SearchS
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search, L.threads, L.lds));
     if (per_cu < 1) return fail(MPAP_ERR_DEVICE, "search kernel does not fit on a CU");
-    L.nblocks = di.cus * std::min(per_cu, per_cu_want);
+    L.nblocks = L.full = di.cus * std::min(per_cu, per_cu_want);
     // merges by halves: each half of a 1024-thread workgroup gets half the
     // LDS, a 512-label chunk and the largest front stage that fits
     // (in 512-thread workgroups, halves of 256 threads were slower: 3D 35.4
@@ -870,7 +870,7 @@ SearchArgs search_args(const mpap_graph *g, Workspace *w, const SearchPrep &p,
     a.qgoff = g->qgoff; a.goal_list = g->goal_list; a.qearly = w->qearly; a.qstop = w->qstop;
     a.early_any = p.early_any ? 1 : 0;
     a.capB = L.capB; a.capC = L.capC; a.nblocks = L.nblocks;
-    a.wcap = L.wcap; a.wslice = L.wslice; a.wmin = wave_min(L); a.wlight = kWaveChildren;
+    a.wcap = L.wcap; a.wslice = L.wslice; a.wmin = wave_min(L);
     a.halves = L.halves; a.half_lds = L.half_lds; a.capBh = L.capBh; a.capCh = L.capCh;
     a.big_front = L.big_front; a.big_children = L.big_children; a.halves_min = L.halves_min;
     a.pool = w->pool; a.pool_cap = w->pool_cap; a.pool_top = w->pool_top; a.nb = w->nb;
@@ -1126,14 +1126,14 @@ int acquire_workspace(mpap_graph *g, const SearchShape &L, Workspace **out) {
             g->spare.pop_back();
         }
     }
-    if (w && w->nblocks != L.nblocks) {
+    if (w && w->nblocks != L.full) {
         w->free_all();
         delete w;
         w = nullptr;
     }
     if (!w) {
         w = new Workspace();
-        const int r = ws_alloc_nodes(w, g->n, L.nblocks);
+        const int r = ws_alloc_nodes(w, g->n, L.full);
         if (r) {
             w->free_all();
             delete w;
@@ -1162,6 +1162,7 @@ int mpap_search_batch(const mpap_graph *gc, const mpap_search_params *sp, int32_
     if ((r = search_shape(p.stage_cap, p.block_threads, p.wave_min_targets, L, p.merge_halves)))
         return r;
     L.obj = uniform_objectives(p);
+    fit_workgroups(L, g->n);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 
     Workspace *w = nullptr;

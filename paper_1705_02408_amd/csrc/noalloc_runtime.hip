@@ -140,6 +140,7 @@ extern "C" int mpap_search_noalloc(const mpap_graph *gc, const mpap_search_param
                           x.merge_halves)))
         return r;
     L.obj = x.n_obj == 2 || x.n_obj == 3 ? x.n_obj : 0;
+    fit_workgroups(L, g->n);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 
     // carve: per-node state, fixed words, then the label stores.  No spill
@@ -148,7 +149,7 @@ extern "C" int mpap_search_noalloc(const mpap_graph *gc, const mpap_search_param
     Carver cv{base, 0, kNoAllocScratchBytes};
     Workspace w;  // pointers into the scratch array only (never freed)
     w.n = n;
-    w.nblocks = L.nblocks;
+    w.nblocks = L.full;
     w.nb = cv.take<int4>(n);
     w.fo = cv.take<int4>(n);
     w.minopen = cv.take<float>(n);
@@ -158,9 +159,9 @@ extern "C" int mpap_search_noalloc(const mpap_graph *gc, const mpap_search_param
     w.acnt = cv.take<int>(2 * kListRegions);
     w.mcur = cv.take<int>(2 * kListRegions);
     w.claim = cv.take<int>(2 * kClaimWords);
-    w.part_cnt = cv.take<long long>(2 * (size_t)L.nblocks);
-    w.part_open = cv.take<long long>(2 * (size_t)L.nblocks);
-    w.part_step = cv.take<long long>(2 * (size_t)L.nblocks);
+    w.part_cnt = cv.take<long long>(2 * (size_t)L.full);
+    w.part_open = cv.take<long long>(2 * (size_t)L.full);
+    w.part_step = cv.take<long long>(2 * (size_t)L.full);
     w.pool_top = cv.take<unsigned>(kBarWords);
     w.bar = cv.take<unsigned>(kBarWords);
     w.err = cv.take<int>(1);

@@ -240,7 +240,10 @@ int mpap_plan_create(mpap_graph *g, const mpap_search_params *sp, int32_t nsp,
     int r = search_prep(g, sp, nsp, p->prep);
     if (!r) r = search_shape(p->prep.stage_cap, p->prep.block_threads, p->prep.wave_min_targets,
                              p->shape, p->prep.merge_halves);
-    if (!r) p->shape.obj = uniform_objectives(p->prep);
+    if (!r) {
+        p->shape.obj = uniform_objectives(p->prep);
+        fit_workgroups(p->shape, g->n);
+    }
     auto bail = [&](int st) {
         mpap_plan_free(p);
         return st;
@@ -287,7 +290,7 @@ int mpap_plan_create(mpap_graph *g, const mpap_search_params *sp, int32_t nsp,
     }
     if (r) return bail(r);
     p->w = new Workspace();
-    if ((r = ws_alloc_nodes(p->w, g->n, p->shape.nblocks))) return bail(r);
+    if ((r = ws_alloc_nodes(p->w, g->n, p->shape.full))) return bail(r);
     if ((r = plan_eager(p, s, nullptr))) return bail(r);
     *out = p;
     return MPAP_OK;

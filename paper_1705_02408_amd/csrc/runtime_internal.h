@@ -395,6 +395,7 @@ struct SearchPrep {
 // Launch shape of the persistent search kernel.
 struct SearchShape {
     int threads = 1024, capC = 1024, capB = 0, nblocks = 0;
+    int full = 0;              // workgroups that fill the chip (workspaces are for these)
     int wcap = 0, wslice = 0;  // single-wave merges: front capacity, LDS slice bytes
     int wmin = 0;              // and the least target count that uses them (see wave_min)
     bool explicit_wmin = false;
@@ -428,26 +429,44 @@ int search_goal_finish(mpap_graph *g, const SearchPrep &p, const SearchShape &L,
 // A search workspace of g for launch shape L (a spare one when it fits).
 int acquire_workspace(mpap_graph *g, const SearchShape &L, Workspace **out);
 GoalArgs goal_args(const mpap_graph *g, Workspace *w);
-// The search kernel build for a launch on g: with single-wave merges only
-// when some iteration can have wave_min targets (or the caller asked for
-// them), with merges by halves on roadmaps of at least 16 nodes per workgroup
-// (smaller ones rarely have iterations with enough targets), or when the
-// caller asked for it.
+// The search kernel build for a launch on g: with single-wave merges when all
+// queries have two objectives, on very large roadmaps, or when the caller
+// asked for them; with merges by halves on roadmaps of at least 16 nodes per
+// workgroup (smaller ones rarely have iterations with enough targets), or when
+// the caller asked for it.
 inline bool halves_build(const SearchShape &L, int n) {
-    return L.halves && (L.halves_forced || n >= 16 * (long long)L.nblocks);
+    return L.halves && (L.halves_forced || n >= 16 * (long long)L.full);
 }
-// The least targets of an iteration that merges by single waves: four waves a
-// target for two objectives (a lane's test of a child is one binary search;
-// 6D roadmap of 20,000 states 7.4, 7.6, 8.0, 8.3 ms at 512, 1,024, 2,048 and
-// 4,096, against 11.9 by halves; 2D of 5,000 samples, whose fronts are long,
-// 9.5, 8.9, 8.9, 8.8 against 8.6), a quarter of one for three, whose children
-// scan prefixes of the front (3D of 20,000 samples 19.5 ms against 12.4).
+// Two objectives: a lane's test of a child is one binary search, and single
+// waves take the light targets of every iteration that has more targets than
+// workgroups (6D roadmap of 8,000 states 5.6 ms, 7.5 by halves; 3D of 1,000
+// samples 1.10, 1.25 by workgroups; 2D of 2,000 samples 3.61 both ways).
+inline bool waves_first(const SearchShape &L) {
+    return L.obj == 2 && L.threads == 1024 && !L.halves_forced;
+}
+// The least targets of an iteration that merges by single waves, where they
+// are not the rule: four waves a target for two objectives, a quarter of one
+// for three, whose children scan prefixes of the front (3D of 20,000 samples
+// 19.5 ms against 12.4).
 inline int wave_min(const SearchShape &L) {
     const int waves = L.nblocks * (L.threads / 64);
-    return L.explicit_wmin ? L.wmin : L.obj == 2 && !L.halves_forced ? waves / 4 : 4 * waves;
+    if (L.explicit_wmin) return L.wmin;
+    if (waves_first(L)) return 1;
+    return L.obj == 2 && !L.halves_forced ? waves / 4 : 4 * waves;
 }
 inline bool wave_build(const SearchShape &L, int n) {
-    return L.wcap > 0 && (L.explicit_wmin || n >= 4 * (long long)wave_min(L));
+    return L.wcap > 0 &&
+           (L.explicit_wmin || waves_first(L) || n >= 4 * (long long)wave_min(L));
+}
+// The workgroups of a search of n nodes: five eighths of the CUs where the
+// grid barriers (5.0 us on 256 workgroups, 3.1 on 128) weigh more than the
+// merges: two objectives below 65,536 nodes (6D of 50,000 states 8.7 ms, 9.6
+// on all CUs; 2D of 500 samples 1.42, 1.53; 3D of 20,000 samples 5.0 both ways;
+// 95,000 nodes of 32 queries 25.1, 21.5) and three below 1,024 (3D of 500
+// samples 0.98, 1.03; from 2,000 on all CUs are better).
+inline void fit_workgroups(SearchShape &L, int n) {
+    if (L.threads != 1024 || L.wcap == 0 || L.explicit_wmin || L.halves_forced) return;
+    if (n < (L.obj == 2 ? 65536 : 1024)) L.nblocks = std::max(1, L.full * 5 / 8);
 }
 // The search build for a launch on g (see search_kernels.h).
 inline const void *search_kernel_for(const SearchShape &L, int n) {

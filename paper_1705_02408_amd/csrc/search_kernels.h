@@ -26,6 +26,11 @@ constexpr int kWeightClasses = 10;
 // (32 planar and spatial queries at once: 25.7 ms at 32, 22.9 at 64, 21.8 at
 // 128, 23.4 at 256; a spatial roadmap of 20,000 samples 6.3, 5.7, 5.1, 4.7 ms).
 constexpr int kWaveChildren = 128;
+// With few targets a workgroup there are waves to spare, and the slowest merge
+// sets the pace: at most this many children for each target a workgroup has
+// (a planar roadmap of 2,000 samples 3.61 ms at 8 or 16, 3.70 at 32, 3.83 with
+// no such limit; a spatial one of 1,000 samples 1.15, 1.10, 1.03, 1.01).
+constexpr int kWaveShare = 16;
 constexpr int kWeightClassBase = 128;
 // Target list regions of n entries each: all targets, one per weight class,
 // and (with merges by halves) two of targets the whole workgroup merges: the
@@ -119,8 +124,6 @@ struct SearchArgs {
     int *claim;        // [2][kClaimWords] single-wave claims by wave parity
     int queue_cap;     // LDS words that select gathers new targets in
     int wcap;          // front labels a wave's slice holds (0: no single-wave merges)
-    int wlight;        // most children of a target merged by a single wave (its front and
-                       // they have to fit the slice together)
     int wmin;          // single-wave merges in iterations with at least wmin targets
     int wslice;        // LDS bytes of one wave's slice in single-wave merges
     // merges by halves (workgroup-only build, 1024-thread workgroups): each

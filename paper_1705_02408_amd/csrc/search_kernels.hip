@@ -1648,6 +1648,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
             // iteration), appended to its class region (one reservation per
             // class present in a wave)
             const int l = lane_id();
+            const int light = min(kWaveChildren, kWaveShare * na / G);
             for (int k0 = b * (int)blockDim.x; k0 < na; k0 += (int)(G * blockDim.x)) {
                 const int k = k0 + threadIdx.x;
                 int c = -1, x = 0;
@@ -1665,7 +1666,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                             else if (wx > a.big_children || fz > a.big_front) c = kWeightClasses + 1;
                         }
                         // light: the front and all its children fit a wave's slice
-                        if (by_wave && wx <= a.wlight && a.nb[x].z + wx <= a.wcap) c = kWeightClasses;
+                        if (by_wave && wx <= light && a.nb[x].z + wx <= a.wcap) c = kWeightClasses;
                         a.wt[x] = 0;
                     } else {
                         atomicOr(a.err, kErrTarget);

@@ -583,10 +583,29 @@ def test_goal_front_over_many_goal_nodes(threads, stage_cap, n_obj, goals):
     dg.close()
 
 
+@pytest.mark.parametrize("n,n_obj,share", [(150, 2, 5), (150, 3, 5), (1022, 3, 5), (1023, 3, 8),
+                                            (1300, 2, 5)])
+def test_workgroups_by_size(n, n_obj, share):
+    """Five eighths of the workgroups for two objectives and for small
+    roadmaps of three, all of them else (the root is one more node): iterations
+    with fewer and with more targets than workgroups, by single waves with two
+    objectives."""
+    env = synth.plain3d(4, n=n)
+    g = ograph.build_graph(env)
+    ref = osearch.search(g, env.beta, n_obj)
+    for lam in (env.lam, 3.0):
+        dg, res = run(g, env.beta, n_obj, radius=env.radius, lam=lam)
+        st = res.stats()
+        assert (st["blocks"], st["wave_build"]) == (256 * share // 8, 1 if n_obj == 2 else 0)
+        check_against_oracle(g, res, ref, env.beta, n_obj)
+        res.close()
+        dg.close()
+
+
 @pytest.mark.parametrize("n_obj,wave", [(2, 1), (3, 0)])
 def test_default_build_by_objectives(n_obj, wave):
-    """From 4,096 nodes on, two-objective searches merge by single waves where
-    an iteration has enough targets; three-objective ones don't."""
+    """Two-objective searches merge by single waves where an iteration has
+    enough targets; three-objective ones of this size don't."""
     env = synth.plain3d(8, n=4500)
     g = ograph.build_graph(env)
     ref = osearch.search(g, env.beta, n_obj)
