@@ -102,6 +102,13 @@ void launch_edge_drift_pairs(const BuildArgs &g, int n, long long pairs, const i
                              hipStream_t s);
 __global__ void k_upper_count(int n, const int *row_ptr, const int *col, int *cnt);
 __global__ void k_node_flags(BuildArgs g, uint8_t *flag);
+__global__ void k_in_count(long long m, const int *col, const float *cost, const float *drift,
+                           int *cnt, unsigned long long *bad);
+__global__ void k_in_scatter(int n, const int *optr, const int *col, const int *rptr, int *fill,
+                             int *edge, int *src);
+__global__ void k_in_place(long long m, const int *col, const float *cost, const float *drift,
+                           const int *rptr, const int *edge, const int *src, int *rsrc,
+                           float *rcost, float *rdrift, int *rperm);
 __global__ void k_flag_list(int n, const uint8_t *flag, unsigned bit, int *list, int *count);
 __global__ void k_scan_block_sums(const int *in, long long n, int *bsum);
 __global__ void k_scan_sums(int *bsum, int nb);

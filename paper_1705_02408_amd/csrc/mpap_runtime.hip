@@ -172,6 +172,8 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
     float *far_tau = nullptr;
     SteerBlob *blob64 = nullptr;
     uint8_t *flag = nullptr;
+    int *in_edge = nullptr, *in_src = nullptr, *in_fill = nullptr;
+    unsigned long long *bad = nullptr;
     // grid of the positions: cubic cells of about 16 states, at most 64 an axis
     GridArgs gr{};
     double extent = 0.0, pos_vol = 1.0, vel_vol = 1.0;
@@ -201,6 +203,7 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
         dfree(d_amp); dfree(ncost); dfree(cost); dfree(drift); dfree(elen); dfree(nbr);
         dfree(ncnt); dfree(rp); dfree(col); dfree(tmp); dfree(err); dfree(flag); dfree(left);
         dfree(far_src); dfree(far_tau); dfree(blob64);
+        dfree(in_edge); dfree(in_src); dfree(in_fill); dfree(bad);
         dfree(gcell); dfree(gslot); dfree(spos); dfree(svel); dfree(gr.ccount); dfree(gr.cstart);
     };
     auto bail = [&](int st) {
@@ -317,28 +320,58 @@ static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *
         k_node_flags<<<div_up(n, 256), 256, 0, s>>>(b, flag);
     }
     HIP_TRY(hipGetLastError());
-    std::vector<int32_t> h_rp(n + 1), h_col(e);
-    std::vector<float> h_cost(e), h_drift(e);
-    std::vector<uint8_t> h_flag(n), h_reset(n), h_goal(n);
-    HIP_TRY(hipMemcpyAsync(h_rp.data(), rp, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s));
-    if (e > 0) {
-        HIP_TRY(hipMemcpyAsync(h_col.data(), col, sizeof(int32_t) * e, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(h_cost.data(), cost, sizeof(float) * e, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(h_drift.data(), drift, sizeof(float) * e, hipMemcpyDeviceToHost, s));
-    }
-    HIP_TRY(hipMemcpyAsync(h_flag.data(), flag, n, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    // the graph: these arrays, the in-edge rows and the goal list
+    mpap_graph *g = new mpap_graph();
+    g->dev = di.dev;
+    g->n = n;
+    g->e = e;
+    auto bail_graph = [&](int st) {
+        graph_release(g);
+        return bail(st);
+    };
+    if ((r = dalloc(&g->rptr, n + 1)) || (r = dalloc(&g->rsrc, e)) ||
+        (r = dalloc(&g->rcost, e)) || (r = dalloc(&g->rdrift, e)) ||
+        (r = dalloc(&g->rperm, e)) || (r = dalloc(&g->goal_list, n)) ||
+        (r = dalloc(&in_edge, e)) || (r = dalloc(&in_src, e)) || (r = dalloc(&in_fill, n)) ||
+        (r = dalloc(&bad, 1)))
+        return bail_graph(r);
+    const unsigned long long none = ~0ull;
+    unsigned long long h_bad = none;
     int n_goal = 0;
-    for (int v = 0; v < n; ++v) {
-        h_reset[v] = h_flag[v] & 1u;
-        h_goal[v] = (h_flag[v] >> 1) & 1u;
-        n_goal += h_goal[v];
+    k_flag_list<<<1, 1024, 0, s>>>(n, flag, 2u, g->goal_list, err);
+    k_zero_i32<<<div_up(n + 1, 256), 256, 0, s>>>(g->rptr, n + 1);  // (stays so without edges)
+    k_zero_i32<<<div_up(n, 256), 256, 0, s>>>(in_fill, n);
+    if ((he = hipMemcpyAsync(bad, &none, sizeof(none), hipMemcpyHostToDevice, s)) != hipSuccess)
+        return bail_graph(fail(MPAP_ERR_HIP, hipGetErrorString(he)));
+    if (e > 0) {
+        k_in_count<<<div_up(e, 256), 256, 0, s>>>(e, col, cost, drift, in_fill, bad);
+        if ((r = scan_i32(in_fill, g->rptr, n, tmp, s))) return bail_graph(r);
+        if ((he = hipMemcpyAsync(g->rptr + n, &e32, sizeof(int), hipMemcpyHostToDevice, s)) !=
+            hipSuccess)
+            return bail_graph(fail(MPAP_ERR_HIP, hipGetErrorString(he)));
+        k_zero_i32<<<div_up(n, 256), 256, 0, s>>>(in_fill, n);
+        k_in_scatter<<<div_up(n, 4), 256, 0, s>>>(n, rp, col, g->rptr, in_fill, in_edge, in_src);
+        k_in_place<<<div_up(e, 256), 256, 0, s>>>(e, col, cost, drift, g->rptr, in_edge, in_src,
+                                                  g->rsrc, g->rcost, g->rdrift, g->rperm);
     }
-    if (n_goal == 0) return bail(fail(MPAP_ERR_NOGOAL, "no roadmap node lies in the goal ball"));
-    mpap_graph *g = nullptr;
-    if ((r = mpap_graph_from_csr(n, h_rp.data(), h_col.data(), h_cost.data(), h_drift.data(),
-                                 h_reset.data(), h_goal.data(), stream, &g)))
-        return bail(r);
+    he = hipGetLastError();
+    if (he == hipSuccess)
+        he = hipMemcpyAsync(&n_goal, err, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (he == hipSuccess)
+        he = hipMemcpyAsync(&h_bad, bad, sizeof(h_bad), hipMemcpyDeviceToHost, s);
+    if (he == hipSuccess) he = hipStreamSynchronize(s);
+    if (he != hipSuccess) return bail_graph(fail(MPAP_ERR_HIP, hipGetErrorString(he)));
+    if (n_goal == 0)
+        return bail_graph(fail(MPAP_ERR_NOGOAL, "no roadmap node lies in the goal ball"));
+    if (h_bad != none)
+        return bail_graph(fail(MPAP_ERR_INVAL, h_bad % 2 ? "edge drift must be finite and >= 0"
+                                                         : "edge cost must be finite and > 0"));
+    g->n_goal = n_goal;
+    if ((r = graph_set_single_query(g))) return bail_graph(r);
+    g->optr = rp; g->ocol = col; g->ocost = cost; g->odrift = drift; g->nflag = flag;
+    rp = col = nullptr;
+    cost = drift = nullptr;
+    flag = nullptr;
     // keep the environment for the surrogate's inputs
     g->dim = 6; g->nbox = env->n_boxes; g->nblob = env->n_blobs;
     g->check_step = gp->check_step; g->reset_q = gp->reset_q; g->radius = gp->radius;

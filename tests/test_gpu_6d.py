@@ -162,3 +162,40 @@ def test_surrogate_on_6d_edges(built):
     assert not rejected
     res.close()
     s.close()
+
+
+@pytest.mark.parametrize("n,k_out,cluster", [(2, 24, False), (66, 64, False), (900, 5, True),
+                                             (900, 24, True)])
+def test_in_edges_of_the_device_build(n, k_out, cluster):
+    """The in-edge rows made on the device against those of the same arrays
+    imported (rows in source order): the same search, label for label, also on
+    the learned drift, which the rows' edge indices carry over."""
+    env = synth.plain6d(2, n=n)
+    pos, vel = env.pos.copy(), env.vel.copy()
+    if cluster:  # few targets for many sources: long in-edge rows
+        pos[: n - 20], vel[: n - 20] = pos[: n - 20] * 0.2 + 0.4, vel[: n - 20] * 0.1
+    env = dataclasses.replace(env, pos=pos, vel=vel, goal=pos[-1].copy(), goal_radius=0.6,
+                              k_out=k_out)
+    dg = mpap.mpap_build_graph(env)
+    got = dg.export()
+    im = mpap.mpap_graph_from_csr(*(got[k] for k in ("row_ptr", "col", "cost", "drift", "reset",
+                                                     "goal")))
+    res = [mpap.mpap_search(g, env.beta, 2, env.radius, env.lam) for g in (dg, im)]
+    st = [r.stats() for r in res]
+    for k in ("front_labels", "labels_expanded", "merges", "candidates", "waves"):
+        assert st[0][k] == st[1][k], k
+    for v in range(0, n + 1 if n > 2 else n, 3):
+        assert np.array_equal(bits(res[0].node_front(v)), bits(res[1].node_front(v))), v
+    model = mpap.Surrogate(seed=3)
+    model.score(dg)
+    sur = mpap.mpap_graph_drift(dg, 1)
+    im2 = mpap.mpap_graph_from_csr(got["row_ptr"], got["col"], got["cost"], sur, got["reset"],
+                                   got["goal"])
+    r1 = mpap.mpap_search(dg, env.beta, 2, env.radius, env.lam, heuristic=1)
+    r2 = mpap.mpap_search(im2, env.beta, 2, env.radius, env.lam)
+    assert np.array_equal(bits(r1.goal_front().vecs), bits(r2.goal_front().vecs))
+    for r in (*res, r1, r2):
+        r.close()
+    for g in (dg, im, im2):
+        g.close()
+    model.close()
