@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(256) k_mlp_loss(MlpDev d, const uint16_t *X, c
 // need these values with the rows as K: they go through LDS, transposed, and
 // each wave sums one 32x32 tile of dW2 (the first two one of dW1) over the
 // workgroup's rows.  Bounded by the latency of this chain: a batch of 4,096
-// rows is 128 waves, 14.3 us.  (Three kernels with the activations in memory
+// rows is 128 waves, 12.2 us.  (Three kernels with the activations in memory
 // and each wave its own partial sums took 43 us; each value's sum over the rows
 // by itself, 160 exchanges for 32 values, and operands gathered two bytes at a
 // time were a good part of it.)
@@ -233,6 +233,19 @@ __global__ void __launch_bounds__(256) k_mlp_train(MlpDev d, MlpTrain t) {
     __shared__ float sb1[kMlpH], sb2[kMlpH], sw3[kMlpH], sb3, red[4][3][kMlpH], redb[4];
     const int l = lane_id(), h = l >> 5, c = l & 31;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int k = 32 * w + c;  // the lane pair's row of the workgroup's
+    // a group's index, then its inputs: two trips to memory, begun before the
+    // weights are waited for
+    bool valid;  // (whole waves)
+    bf16x8 bx;
+    float want;
+    auto fetch = [&](int b) {
+        valid = b < t.B;
+        const long long row = valid ? t.idx[b] : 0;
+        bx = valid ? load8(t.X + row * kMlpIn + 8 * h) : zero8();
+        want = valid ? t.t[row] : 0.0f;
+    };
+    fetch((int)blockIdx.x * kTrainRows + k);
     Frags f;
     load_frags(d, l, f);
     // W2 with rows hidden, K over the outputs in the accumulators' order
@@ -253,12 +266,7 @@ __global__ void __launch_bounds__(256) k_mlp_train(MlpDev d, MlpTrain t) {
     f32x16 g2 = {}, g1 = {};  // this wave's tile of dW2^T and dW1^T
     float s3 = 0.0f, s2 = 0.0f, s1 = 0.0f, gb3 = 0.0f;
     for (int r0 = (int)blockIdx.x * kTrainRows; r0 < t.B; r0 += (int)gridDim.x * kTrainRows) {
-        const int k = 32 * w + c;  // the lane pair's row of the workgroup's
         const int b = r0 + k;
-        const bool valid = b < t.B;  // (whole waves)
-        const long long row = valid ? t.idx[b] : 0;
-        const bf16x8 bx = valid ? load8(t.X + row * kMlpIn + 8 * h) : zero8();
-        const float want = valid ? t.t[row] : 0.0f;
         {
             const uint4 raw = __builtin_bit_cast(uint4, bx);
             const uint32_t x[4] = {raw.x, raw.y, raw.z, raw.w};
@@ -270,10 +278,7 @@ __global__ void __launch_bounds__(256) k_mlp_train(MlpDev d, MlpTrain t) {
         uint16_t h1[2][16];
         const float y = forward32(f, bx, sb1, sb2, sw3, sb3, h, d1, h1, z2);
         const float dy = valid ? inv * (y - want) : 0.0f;
-        if (h == 0 && valid) {
-            t.y[b] = y;
-            gb3 += dy;
-        }
+        if (h == 0) gb3 += dy;
         float v3[32], v2[32], v1[32];
         bf16x8 bz[2][2];
 #pragma unroll
@@ -283,7 +288,8 @@ __global__ void __launch_bounds__(256) k_mlp_train(MlpDev d, MlpTrain t) {
             for (int v = 0; v < 16; ++v) {
                 const int o = 32 * to + rowmap(v, h);
                 const float z = z2[to][v];
-                const float dz = z > 0.0f ? dy * sw3[o] : 0.0f;
+                const float pass = dy * sw3[o];  // (read by every lane: no branch)
+                const float dz = z > 0.0f ? pass : 0.0f;
                 dzb[v] = f2bf(dz);
                 sdz2[o][k] = dzb[v];
                 sh1[o][k] = h1[to][v];
@@ -319,6 +325,9 @@ __global__ void __launch_bounds__(256) k_mlp_train(MlpDev d, MlpTrain t) {
                 g1 = mfma(load8(&sdz1[32 * w + c][kk]), c < kMlpIn ? load8(&sx[c][kk]) : zero8(), g1);
         }
         __syncthreads();
+        // (not before: a barrier waits for stores on their way)
+        if (h == 0 && valid) t.y[b] = y;
+        fetch(b + (int)gridDim.x * kTrainRows);
     }
     float *part = t.part + (size_t)blockIdx.x * kGradWords;
 #pragma unroll
@@ -348,7 +357,7 @@ __global__ void __launch_bounds__(256) k_mlp_train(MlpDev d, MlpTrain t) {
 
 // Sum the workgroups' partials in a fixed order, then (optionally) one Adam
 // step on the float32 masters and a refresh of the bfloat16 copies.  64
-// parameters a block, each by eight threads: 4.1 us a batch of 4,096 rows (16.3
+// parameters a block, each by eight threads: 3.9 us a batch of 4,096 rows (16.3
 // with a thread a parameter, all partials one after the other).
 __global__ void __launch_bounds__(512) k_mlp_adam(MlpAdam a) {
     __shared__ float red[8][64];
