@@ -88,8 +88,8 @@ __global__ void k_sort_rows(int n, const int *off, const int *cnt, int *cand_v, 
 __global__ void k_near_count(BuildArgs g, int *cnt);
 __global__ void k_near_fill(BuildArgs g, const int *off, int *cand_u, int *cand_v,
                             float *cand_c);
-__global__ void k_collide(BuildArgs g, long long m, const int *cand_u, const int *cand_v,
-                          const float *cand_c, int *keep);
+void launch_collide(const BuildArgs &g, long long m, const int *cand_u, const int *cand_v,
+                    const float *cand_c, int *keep, hipStream_t s);
 __global__ void k_compact_edges(long long m, const int *keep, const int *kscan,
                                 const int *cand_v, const float *cand_c, int *col, float *cost);
 __global__ void k_row_ptr(int n, long long m, const int *cand_off, const int *kscan,

@@ -465,57 +465,93 @@ __global__ void __launch_bounds__(256) k_near_fill(BuildArgs g, const int *off, 
 
 // Collision(a, b), (a, b) the candidate pair in id order: points
 // x_a + (k/K)(x_b - x_a), k = 0..K, K = ceil(cost/step), against closed boxes.
+// A wave's 64 candidates have one or two sources and lie within the radius of
+// them: the boxes that miss the wave's common range are left out 64 at a time
+// (2.1 million candidates, 100 boxes: 59 us; each candidate against each box
+// 472 us).
+template <int D>
 __global__ void __launch_bounds__(256) k_collide(BuildArgs g, long long m, const int *cand_u,
                                                  const int *cand_v, const float *cand_c,
                                                  int *keep) {
     extern __shared__ float boxes[];  // lo[nbox*dim], hi[nbox*dim]
-    for (int i = threadIdx.x; i < g.nbox * g.dim; i += blockDim.x) {
+    for (int i = threadIdx.x; i < g.nbox * D; i += blockDim.x) {
         boxes[i] = g.blo[i];
-        boxes[g.nbox * g.dim + i] = g.bhi[i];
+        boxes[g.nbox * D + i] = g.bhi[i];
     }
     __syncthreads();
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= m) return;
-    const int u = cand_u[e], v = cand_v[e];
-    const int a = min(u, v), b = max(u, v);
-    float xa[3] = {0.f, 0.f, 0.f}, df[3] = {0.f, 0.f, 0.f};
-    for (int k = 0; k < g.dim; ++k) {
-        xa[k] = g.pos[a * g.dim + k];
-        df[k] = g.pos[b * g.dim + k] - xa[k];
-    }
-    int K = (int)ceilf(cand_c[e] / g.step);
-    if (K < 1) K = 1;
-    const float fK = (float)K;
+    const bool in_list = e < m;
+    float xa[D] = {}, df[D] = {}, fK = 1.0f;
     // Each rounded coordinate xa + t df is monotone in s (t = s/K rounded,
     // t = 1 at s = K), so the points lie between the first (xa) and the
     // last (xa + df rounded) on every axis: a box missing that range on an
     // axis holds none of them.  The boxes are taken one at a time and only
     // those meeting the range are tested point by point (the same set of
     // point-in-box tests, grouped by box).
-    float plo[3] = {0.f, 0.f, 0.f}, phi[3] = {0.f, 0.f, 0.f};
-    for (int k = 0; k < g.dim; ++k) {
-        const float last = xa[k] + df[k];
-        plo[k] = fminf(xa[k], last);
-        phi[k] = fmaxf(xa[k], last);
+    float plo[D], phi[D];
+    for (int k = 0; k < D; ++k) {
+        plo[k] = MPAP_INF;  // (meets no box)
+        phi[k] = -MPAP_INF;
+    }
+    int K = 1;
+    if (in_list) {
+        const int u = cand_u[e], v = cand_v[e];
+        const int a = min(u, v), b = max(u, v);
+        for (int k = 0; k < D; ++k) {
+            xa[k] = g.pos[a * D + k];
+            df[k] = g.pos[b * D + k] - xa[k];
+            const float last = xa[k] + df[k];
+            plo[k] = fminf(xa[k], last);
+            phi[k] = fmaxf(xa[k], last);
+        }
+        K = (int)ceilf(cand_c[e] / g.step);
+        if (K < 1) K = 1;
+        fK = (float)K;
+    }
+    float wlo[D], whi[D];
+    for (int k = 0; k < D; ++k) {
+        wlo[k] = wave_min(plo[k]);
+        whi[k] = -wave_min(-phi[k]);
     }
     bool hit = false;
-    for (int j = 0; j < g.nbox && !hit; ++j) {
-        const float *lo = &boxes[j * g.dim];
-        const float *hi = &boxes[g.nbox * g.dim + j * g.dim];
-        bool meets = true;
-        for (int k = 0; k < g.dim; ++k) meets = meets && phi[k] >= lo[k] && plo[k] <= hi[k];
-        if (!meets) continue;
-        for (int s = 0; s <= K && !hit; ++s) {
-            const float t = (float)s / fK;
-            bool in = true;
-            for (int k = 0; k < g.dim; ++k) {
-                const float p = xa[k] + t * df[k];
-                in = in && (p >= lo[k]) && (p <= hi[k]);
+    for (int j0 = 0; j0 < g.nbox; j0 += 64) {
+        const int jl = j0 + lane_id();
+        bool near = jl < g.nbox;
+        if (near)
+            for (int k = 0; k < D; ++k)
+                near = near && whi[k] >= boxes[jl * D + k] &&
+                       wlo[k] <= boxes[g.nbox * D + jl * D + k];
+        uint64_t todo = ballot64(near);
+        while (todo) {
+            const int j = j0 + (int)__ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            float lo[D], hi[D];
+            bool meets = !hit;
+            for (int k = 0; k < D; ++k) {
+                lo[k] = boxes[j * D + k];
+                hi[k] = boxes[g.nbox * D + j * D + k];
+                meets = meets && phi[k] >= lo[k] && plo[k] <= hi[k];
             }
-            hit = in;
+            if (!meets) continue;
+            for (int s = 0; s <= K && !hit; ++s) {
+                const float t = (float)s / fK;
+                bool in = true;
+                for (int k = 0; k < D; ++k) {
+                    const float p = xa[k] + t * df[k];
+                    in = in && (p >= lo[k]) && (p <= hi[k]);
+                }
+                hit = in;
+            }
         }
     }
-    keep[e] = hit ? 0 : 1;
+    if (in_list) keep[e] = hit ? 0 : 1;
+}
+void launch_collide(const BuildArgs &g, long long m, const int *cand_u, const int *cand_v,
+                    const float *cand_c, int *keep, hipStream_t s) {
+    const size_t lds = sizeof(float) * 2 * (size_t)g.nbox * g.dim;
+    const unsigned blocks = (unsigned)((m + 255) / 256);
+    if (g.dim == 2) k_collide<2><<<blocks, 256, lds, s>>>(g, m, cand_u, cand_v, cand_c, keep);
+    else k_collide<3><<<blocks, 256, lds, s>>>(g, m, cand_u, cand_v, cand_c, keep);
 }
 
 __global__ void __launch_bounds__(256) k_compact_edges(long long m, const int *keep,

@@ -534,8 +534,7 @@ int mpap_build_graph(const mpap_env *env, const mpap_graph_params *gp, void *str
     } else
         k_near_fill<<<nblk, 256, 0, s>>>(a, coff, cand_u, cand_v, cand_c);
     if (m > 0) {
-        const size_t lds = sizeof(float) * 2 * nb_;
-        k_collide<<<div_up(m, 256), 256, lds, s>>>(a, m, cand_u, cand_v, cand_c, keep);
+        launch_collide(a, m, cand_u, cand_v, cand_c, keep, s);
         if ((r = scan_i32(keep, kscan, m, tmp, s))) return bail(r);
     }
     int last_keep = 0, last_ks = 0;

@@ -306,8 +306,7 @@ int mpap_graph_add_boxes(const mpap_graph *gc, int32_t n_boxes, const float *box
         k_edge_sources<<<div_up(n, 256), 256, 0, s>>>(n, g->optr, src);
         // Collision against the new boxes only (Alg. 2 Collision; the earlier
         // boxes were tested when the roadmap was built)
-        k_collide<<<div_up(m, 256), 256, sizeof(float) * 2 * nb_, s>>>(a, m, src, g->ocol,
-                                                                       g->ocost, keep);
+        launch_collide(a, m, src, g->ocol, g->ocost, keep, s);
         if ((r = scan_i32(keep, kscan, m, tmp, s))) return bail(r);
         int last_keep = 0, last_ks = 0;
         HIP_TRY(hipMemcpyAsync(&last_keep, keep + (m - 1), sizeof(int), hipMemcpyDeviceToHost, s));

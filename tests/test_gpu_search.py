@@ -282,6 +282,29 @@ def test_build_graph_matches_oracle(dim, n, seed):
     assert np.array_equal(got["reset"], ref["reset"])
 
 
+@pytest.mark.parametrize("dim,n,boxes", [(2, 300, 0), (2, 300, 1), (2, 700, 64), (3, 700, 65),
+                                         (3, 40, 129), (3, 1500, 200)])
+def test_obstacles_by_the_wave(dim, n, boxes):
+    """Edges against 0 to 200 boxes (none, one word of 64, one more, several;
+    waves with one source, with many and partly filled), some of them thin,
+    some touching samples: the oracle's edges."""
+    env = synth.plain2d(17, n=n) if dim == 2 else synth.plain3d(17, n=n)
+    rng = np.random.default_rng(boxes)
+    lo = rng.uniform(0.0, 0.95, (boxes, dim)).astype(np.float32)
+    hi = lo + rng.choice([0.0, 0.002, 0.03, 0.08], (boxes, dim)).astype(np.float32)
+    if boxes > 1:
+        lo[1] = hi[1] = env.pos[5]
+    env = dataclasses.replace(env, box_lo=lo, box_hi=hi, goal=env.pos[-1].copy(),
+                              goal_radius=0.3)
+    ref = ograph.build_graph(env)
+    dg = mpap.mpap_build_graph(env)
+    got = dg.export()
+    for k in ("row_ptr", "col"):
+        assert np.array_equal(got[k], ref[k]), k
+    assert np.array_equal(bits(got["cost"]), bits(ref["cost"]))
+    dg.close()
+
+
 @pytest.mark.parametrize("dim,n,what", [
     (2, 400, "many points"), (3, 300, "many points"), (2, 400, "narrow blobs"),
     (3, 300, "narrow blobs"), (2, 400, "far blobs"), (3, 300, "no blobs"),
