@@ -684,17 +684,31 @@ __global__ void __launch_bounds__(256) k_in_place(long long m, const int *col, c
     rperm[q] = k;
 }
 
-// Ordered list of the nodes with flag bit `bit` set (single block).
+// Ordered list of the nodes with flag bit `bit` set (single block; 16 flags a
+// thread: 50,000 nodes in four rounds, 9 us; one flag a thread 59).  flag is
+// 16-byte aligned.
 __global__ void __launch_bounds__(1024) k_flag_list(int n, const uint8_t *flag, unsigned bit,
                                                     int *list, int *count) {
     __shared__ int scan[32];
     int carry = 0;
-    for (int t0 = 0; t0 < n; t0 += blockDim.x) {
-        const int v = t0 + threadIdx.x;
-        const int f = (v < n && (flag[v] & bit)) ? 1 : 0;
+    for (int t0 = 0; t0 < n; t0 += 16 * (int)blockDim.x) {
+        const int v0 = t0 + 16 * (int)threadIdx.x;
+        unsigned w[4] = {0u, 0u, 0u, 0u};
+        if (v0 + 16 <= n) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(flag + v0);
+            w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+        } else {
+            for (int i = 0; i < 16; ++i)
+                if (v0 + i < n) w[i >> 2] |= (unsigned)flag[v0 + i] << (8 * (i & 3));
+        }
+        const unsigned each = 0x01010101u * bit;
+        int mine = 0;
+        for (int i = 0; i < 4; ++i) mine += __popc(w[i] & each);
         int tot;
-        const int ex = block_excl_scan(f, scan, &tot);
-        if (f) list[carry + ex] = v;
+        int o = carry + block_excl_scan(mine, scan, &tot);
+        if (mine)
+            for (int i = 0; i < 16; ++i)
+                if ((w[i >> 2] >> (8 * (i & 3))) & bit) list[o++] = v0 + i;
         carry += tot;
     }
     if (threadIdx.x == 0) *count = carry;

@@ -282,6 +282,30 @@ def test_build_graph_matches_oracle(dim, n, seed):
     assert np.array_equal(got["reset"], ref["reset"])
 
 
+@pytest.mark.parametrize("n", [14, 15, 16, 17, 16383, 16384])
+def test_goal_list_of_built_roadmaps(n):
+    """The goal front of roadmaps whose node count (n + 1) lies around the 16
+    flags a thread reads and the 16,384 of a round: the minimum over the nodes
+    that the goal mask names, the last sample among them."""
+    env = synth.plain2d(23, n=n)
+    env = dataclasses.replace(env, goal=env.pos[-1].copy(), goal_radius=0.2 if n < 100 else 0.06,
+                              box_lo=env.box_lo[:0], box_hi=env.box_hi[:0])
+    dg = mpap.mpap_build_graph(env)
+    goal = np.flatnonzero(dg.export()["goal"])
+    assert goal[-1] == n and dg.info()["n_goal"] == goal.size
+    res = mpap.mpap_search(dg, np.inf, 2, env.radius, 4.0)
+    vecs = np.concatenate([res.node_front(int(v)) for v in goal])
+    vecs = sort_lex(vecs)
+    want, best = [], np.inf
+    for row in vecs:
+        if row[1] < best:
+            want.append(row)
+            best = row[1]
+    assert np.array_equal(bits(res.goal_front().vecs), bits(np.array(want).reshape(-1, 3)))
+    res.close()
+    dg.close()
+
+
 @pytest.mark.parametrize("dim,n,boxes", [(2, 300, 0), (2, 300, 1), (2, 700, 64), (3, 700, 65),
                                          (3, 40, 129), (3, 1500, 200)])
 def test_obstacles_by_the_wave(dim, n, boxes):
