@@ -81,6 +81,7 @@ constexpr int kGridSortMax = 256;
 
 __global__ void k_grid_bin(BuildArgs g, GridArgs gr, int *cell, int *slot);
 __global__ void k_grid_scatter(BuildArgs g, GridArgs gr, const int *cell, const int *slot);
+constexpr int kNearLanes = 8;  // lanes that share a node in the next two
 __global__ void k_near_count_grid(BuildArgs g, GridArgs gr, int *cnt, int *max_cnt);
 __global__ void k_near_fill_grid(BuildArgs g, GridArgs gr, const int *off, int *cand_u,
                                  int *cand_v, float *cand_c);

@@ -39,8 +39,8 @@ __device__ __forceinline__ int cell_coords(const GridArgs &gr, const float *x, i
     return (cz * gr.gy + cy) * gr.gx + cx;
 }
 
-// f(j) for every sorted slot j of the cells adjacent to (cx, cy, cz), the
-// cell itself included: per (y, z) row of cells one contiguous run
+// f(b, e) for every run [b, e) of sorted slots of the cells adjacent to
+// (cx, cy, cz), the cell itself included: one per (y, z) row of cells
 template <class F>
 __device__ __forceinline__ void for_adjacent(const GridArgs &gr, int cx, int cy, int cz, F f) {
     const int x0 = max(cx - 1, 0), x1 = min(cx + 1, gr.gx - 1);
@@ -50,7 +50,7 @@ __device__ __forceinline__ void for_adjacent(const GridArgs &gr, int cx, int cy,
             const int row = (z * gr.gy + y) * gr.gx;
             const int b = gr.cstart[row + x0];
             const int e = gr.cstart[row + x1] + gr.ccount[row + x1];
-            for (int j = b; j < e; ++j) f(j);
+            f(b, e);
         }
 }
 
@@ -332,12 +332,15 @@ __global__ void __launch_bounds__(256) k_grid_scatter(BuildArgs g, GridArgs gr, 
 }
 
 // Step 3: the Near count of each node (the same test as the all-pairs
-// kernel on the candidates of the adjacent cells); threads take nodes in
-// cell order so the lanes of a wave scan the same cells.  max_cnt gets the
-// longest row.
+// kernel on the candidates of the adjacent cells); kNearLanes lanes share a
+// node's candidates, and nodes are taken in cell order so the lanes of a wave
+// scan the same cells.  A thread per node was bound by its chain of loads:
+// 33 us for 50,000 samples in 3D (125), 9 for 2,000 in 2D (32); step 4
+// 37 (137) and 8 (35).  max_cnt gets the longest row.
 __global__ void __launch_bounds__(256) k_near_count_grid(BuildArgs g, GridArgs gr, int *cnt,
                                                          int *max_cnt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kNearLanes);
+    const int sub = (int)threadIdx.x % kNearLanes;
     int c = 0;
     if (i < g.n) {
         const int u = gr.sid[i];
@@ -345,41 +348,64 @@ __global__ void __launch_bounds__(256) k_near_count_grid(BuildArgs g, GridArgs g
         const float xu[3] = {p.x, p.y, p.z};
         int cx, cy, cz;
         cell_coords(gr, xu, g.dim, cx, cy, cz);
-        for_adjacent(gr, cx, cy, cz, [&](int j) {
-            const float4 q = gr.spos[j];
-            const float xv[3] = {q.x, q.y, q.z};
-            const float cost = sqrtf(sqdist(xu, xv, g.dim));
-            c += (cost < g.r && gr.sid[j] != u) ? 1 : 0;
+        for_adjacent(gr, cx, cy, cz, [&](int j0, int j1) {
+            for (int j = j0 + sub; j < j1; j += kNearLanes) {
+                const float4 q = gr.spos[j];
+                const float xv[3] = {q.x, q.y, q.z};
+                const float cost = sqrtf(sqdist(xu, xv, g.dim));
+                c += (cost < g.r && gr.sid[j] != u) ? 1 : 0;
+            }
         });
-        cnt[u] = c;
+        for (int o = kNearLanes / 2; o > 0; o >>= 1) c += __shfl_xor(c, o);
+        if (sub == 0) cnt[u] = c;
     }
-    for (int o = 32; o > 0; o >>= 1) c = max(c, __shfl_xor(c, o));
-    if ((threadIdx.x & 63) == 0) atomicMax(max_cnt, c);
+    for (int o = 32; o >= kNearLanes; o >>= 1) c = max(c, __shfl_xor(c, o));
+    // (atomics at one address wait for each other, 12 ns each: only those
+    // that may raise it)
+    if ((threadIdx.x & 63) == 0 &&
+        c > __hip_atomic_load(max_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(max_cnt, c);
 }
 
-// Step 4: the candidates of each node written to its row at off[u] in the
-// order the cells are scanned.
+// Step 4: the candidates of each node written to its row at off[u] (step 5
+// orders them).
 __global__ void __launch_bounds__(256) k_near_fill_grid(BuildArgs g, GridArgs gr, const int *off,
                                                         int *cand_u, int *cand_v, float *cand_c) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kNearLanes);
+    const int sub = (int)threadIdx.x % kNearLanes;
     if (i >= g.n) return;
     const int u = gr.sid[i];
     const float4 p = gr.spos[i];
     const float xu[3] = {p.x, p.y, p.z};
     int cx, cy, cz;
     cell_coords(gr, xu, g.dim, cx, cy, cz);
-    const int o = off[u];
-    int k = 0;
-    for_adjacent(gr, cx, cy, cz, [&](int j) {
-        const int v = gr.sid[j];
-        const float4 q = gr.spos[j];
-        const float xv[3] = {q.x, q.y, q.z};
-        const float cost = sqrtf(sqdist(xu, xv, g.dim));
-        if (cost < g.r && v != u) {
-            cand_u[o + k] = u;
-            cand_v[o + k] = v;
-            cand_c[o + k] = cost;
-            ++k;
+    // the node's lanes within the wave, and those below this one
+    const int first = lane_id() - sub;
+    const uint64_t lanes = ((1ull << kNearLanes) - 1ull) << first;
+    const uint64_t below = ((1ull << sub) - 1ull) << first;
+    int o = off[u];
+    for_adjacent(gr, cx, cy, cz, [&](int j0, int j1) {
+        for (int jb = j0; jb < j1; jb += kNearLanes) {
+            const int j = jb + sub;
+            bool take = j < j1;
+            int v = u;
+            float cost = 0.f;
+            if (take) {
+                v = gr.sid[j];
+                const float4 q = gr.spos[j];
+                const float xv[3] = {q.x, q.y, q.z};
+                cost = sqrtf(sqdist(xu, xv, g.dim));
+                take = cost < g.r && v != u;
+            }
+            // (a node's lanes stay together: the same cells and trips)
+            const uint64_t tk = __ballot(take) & lanes;
+            if (take) {
+                const int at = o + (int)__popcll(tk & below);
+                cand_u[at] = u;
+                cand_v[at] = v;
+                cand_c[at] = cost;
+            }
+            o += (int)__popcll(tk);
         }
     });
 }

@@ -511,7 +511,7 @@ int mpap_build_graph(const mpap_env *env, const mpap_graph_params *gp, void *str
         k_grid_bin<<<nblk, 256, 0, s>>>(a, gr, gcell, gslot);
         if ((r = scan_i32(gr.ccount, gr.cstart, gr.ncell, tmp, s))) return bail(r);
         k_grid_scatter<<<nblk, 256, 0, s>>>(a, gr, gcell, gslot);
-        k_near_count_grid<<<nblk, 256, 0, s>>>(a, gr, cnt, maxc);
+        k_near_count_grid<<<div_up((long long)kNearLanes * n, 256), 256, 0, s>>>(a, gr, cnt, maxc);
     } else {
         k_near_count<<<nblk, 256, 0, s>>>(a, cnt);
     }
@@ -529,7 +529,8 @@ int mpap_build_graph(const mpap_env *env, const mpap_graph_params *gp, void *str
     dfree(tmp);
     if ((r = dalloc(&tmp, div_up(std::max(m, 1LL), kScanTile) + 1))) return bail(r);
     if (use_grid && max_row <= kGridSortMax) {
-        k_near_fill_grid<<<nblk, 256, 0, s>>>(a, gr, coff, cand_u, cand_v, cand_c);
+        k_near_fill_grid<<<div_up((long long)kNearLanes * n, 256), 256, 0, s>>>(a, gr, coff, cand_u,
+                                                                               cand_v, cand_c);
         k_sort_rows<<<div_up(n, 4), 256, 0, s>>>(n, coff, cnt, cand_v, cand_c);
     } else
         k_near_fill<<<nblk, 256, 0, s>>>(a, coff, cand_u, cand_v, cand_c);
