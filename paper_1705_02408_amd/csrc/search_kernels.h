@@ -17,11 +17,12 @@ constexpr int kErrPool = 2;     // bucket pool exhausted
 constexpr int kErrTimeout = 4;  // a grid or half-workgroup barrier wait exceeded its bound
 constexpr int kErrTarget = 8;   // a queued merge target is not a node (internal error)
 
-// Merge targets of a workgroup-only launch are ordered by expected work (the
-// children queued to them): class 0 below kWeightClassBase children, class c
-// from kWeightClassBase * 2^(c-1) on, the last class open-ended.  Heavier
-// classes are merged first, so the longest merges of an iteration start early.
+// Merge targets are ordered by expected work (the children queued to them):
+// class 0 below kWeightClassBase children, class c from
+// kWeightClassBase * 2^(c-1) on, the last class open-ended.  Heavier classes
+// are merged first, so the longest merges of an iteration start early.
 constexpr int kWeightClasses = 10;
+constexpr int kWeightClassBase = 128;
 // Most children of a target that one wave merges; above, a whole workgroup
 // (32 planar and spatial queries at once: 25.7 ms at 32, 22.9 at 64, 21.8 at
 // 128, 23.4 at 256; a spatial roadmap of 20,000 samples 6.3, 5.7, 5.1, 4.7 ms).
@@ -31,7 +32,6 @@ constexpr int kWaveChildren = 128;
 // (a planar roadmap of 2,000 samples 3.61 ms at 8 or 16, 3.70 at 32, 3.83 with
 // no such limit; a spatial one of 1,000 samples 1.15, 1.10, 1.03, 1.01).
 constexpr int kWaveShare = 16;
-constexpr int kWeightClassBase = 128;
 // Target list regions of n entries each: all targets, one per weight class,
 // and (with merges by halves) two of targets the whole workgroup merges: the
 // heavy ones (first), then the rest.

@@ -622,7 +622,7 @@ __device__ __forceinline__ bool near_dead(const float4 *B, int nB, const float4 
 // `prescanned`: the candidates have passed the first test already (none
 // dead, the undecided ones listed in u_idx[0..misc[6]) with their u_end).
 // kWide: the all-pairs survivor step keeps four reads in flight (more
-// registers; the wave-first build, whose single-wave merges share the
+// registers; the wave build, whose single-wave merges share the
 // kernel, keeps one).
 template <bool kWide, bool kHalf>
 __device__ __forceinline__ bool merge_chunk(MergeLds &s, Grp<kHalf> &gp, int &nB, int nC, int near_scan,
@@ -857,11 +857,10 @@ __device__ __forceinline__ bool merge_chunk(MergeLds &s, Grp<kHalf> &gp, int &nB
 }
 
 // ------------------------------------------------ single-wave merges (small fronts)
-// A target whose front holds at most wcap labels is merged by one wave in its
-// own LDS slice, without workgroup barriers, so the 16 waves of a workgroup
-// merge 16 targets at once.  The steps are those of merge_chunk, per chunk
-// of 64 children (one per lane).  A front that would outgrow the slice is
-// left untouched (nothing is written back) and handed to the workgroup path.
+// A target whose front and new children together fit wcap labels is merged by
+// one wave in its own LDS slice, without workgroup barriers, so the 16 waves of
+// a workgroup merge 16 targets at once.  The steps are those of merge_chunk, per
+// chunk of 64 children (one per lane).
 struct WaveLds {
     float4 *B;    // [wcap] the front, lexicographic order
     float4 *C;    // [64] the chunk's children
@@ -908,9 +907,9 @@ __device__ void wave_seg_summary(const WaveLds &W, int n) {
     wsync();
 }
 
-// Returns false when the front would outgrow the slice (the target then
-// goes to the workgroup path; nothing has been written).  kObj: 2 or 3 when
-// every query has that many objectives, 0 when the query decides.
+// Returns false, and has written nothing, when the front would outgrow the
+// slice (an internal error: the target's weight said that it fits).  kObj: 2 or
+// 3 when every query has that many objectives, 0 when the query decides.
 template <int kObj>
 __device__ bool wave_merge_node(const SearchArgs &a, int x, int wave, const WaveLds &W,
                                 long long &cand_out) {
@@ -1648,7 +1647,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
             // iteration), appended to its class region (one reservation per
             // class present in a wave)
             const int l = lane_id();
-            const int light = min(kWaveChildren, kWaveShare * na / G);
+            const int light = (int)min((long long)kWaveChildren, (long long)kWaveShare * na / G);
             for (int k0 = b * (int)blockDim.x; k0 < na; k0 += (int)(G * blockDim.x)) {
                 const int k = k0 + threadIdx.x;
                 int c = -1, x = 0;
@@ -1790,7 +1789,7 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
                 MergeLds s;
                 carve_lds(lds, a, s);
                 Grp<false> gw = whole_group();
-                // (the wave-first build and the halves builds for two or
+                // (the wave build and the halves builds for two or
                 // either objective count keep the single-read survivor step:
                 // the four-read one needs more registers than they leave)
                 merge_node<!kWaveMerges && (!kHalves || kObj == 3), kObj>(a, cmd, wave, s, gw, st_cand);
@@ -1911,12 +1910,11 @@ __device__ __forceinline__ void search_body(SearchArgs a) {
     }
 }
 
-// The builds of the persistent search: with single-wave merges for
-// iterations with many small targets (large batches); the workgroup path
-// only; and the workgroup path with merges by halves (two targets at once per
-// workgroup in iterations with enough of them); each for queries of two
-// objectives, of three, or of either (decided per query).  Each build gets
-// its own register allocation.
+// The builds of the persistent search: with single-wave merges of the light
+// targets (two objectives, very large batches); the workgroup path only; and the
+// workgroup path with merges by halves (two targets at once per workgroup in
+// iterations with enough of them); each for queries of two objectives, of three,
+// or of either (decided per query).  Each build gets its own register allocation.
 __global__ void __launch_bounds__(1024) k_search(SearchArgs a) { search_body<false, false, 0>(a); }
 __global__ void __launch_bounds__(1024) k_search_o2(SearchArgs a) {
     search_body<false, false, 2>(a);
