@@ -110,75 +110,109 @@ __device__ __forceinline__ BuildArgs stage_blobs(const BuildArgs &g, float *blob
     return gl;
 }
 
-// midpoints whose quality sums one pass over the blobs holds in registers
+// midpoints whose quality sums one pass over the blobs holds in registers, and
+// the place of a run's anchor among them
 constexpr int kDriftRun = 16;
+constexpr int kDriftMid = 8;
 
-// exp(-x) for 0 <= x <= 1/64: its series to the seventh power (the next term
-// is below 2^-63)
-__device__ __forceinline__ double exp_small(double x) {
-    double p = 1.0 / 5040.0;
-    p = __builtin_fma(-x, p, 1.0 / 720.0);
-    p = __builtin_fma(-x, p, 1.0 / 120.0);
-    p = __builtin_fma(-x, p, 1.0 / 24.0);
-    p = __builtin_fma(-x, p, 1.0 / 6.0);
-    p = __builtin_fma(-x, p, 0.5);
-    p = __builtin_fma(-x, p, 1.0);
-    return __builtin_fma(-x, p, 1.0);
+// 1 / n!, n <= 18
+constexpr double inv_factorial(int n) {
+    double f = 1.0;
+    for (int i = 2; i <= n; ++i) f *= (double)i;
+    return 1.0 / f;
 }
+// e^(-u - v) - 1, e^(u - v) - 1 and e^-2v - 1 for 0 <= v <= 1/128, from the
+// series of sinh u (to u^13), cosh u - 1 (to u^14) and e^-v - 1 (to v^6)
+__device__ __forceinline__ void expm1_both(double u, double v, double &down, double &up,
+                                           double &twice) {
+    const double z = u * u;
+    double sh = inv_factorial(13), ch = inv_factorial(14), m = inv_factorial(6);
+#pragma unroll
+    for (int n = 11; n >= 3; n -= 2) sh = __builtin_fma(z, sh, inv_factorial(n));
+#pragma unroll
+    for (int n = 12; n >= 4; n -= 2) ch = __builtin_fma(z, ch, inv_factorial(n));
+#pragma unroll
+    for (int n = 5; n >= 2; --n) m = __builtin_fma(-v, m, inv_factorial(n));
+    sh = __builtin_fma(z * u, sh, u);
+    ch = z * __builtin_fma(z, ch, 0.5);
+    m = __builtin_fma(v * v, m, -v);
+    const double a = ch - sh, b = ch + sh;
+    down = __builtin_fma(a, m, a + m);
+    up = __builtin_fma(b, m, b + m);
+    twice = __builtin_fma(m, m, 2.0 * m);
+}
+
+// sum over the four lanes of a quad, in each of them (every lane of the wave calls)
+template <int kPerm>
+__device__ __forceinline__ double quad_perm(double v) {
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(v), kPerm, 0xf, 0xf, false),
+        __builtin_amdgcn_update_dpp(0, __double2loint(v), kPerm, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double quad_sum(double v) {
+    v += quad_perm<0xb1>(v);         // lanes 1, 0, 3, 2
+    return v + quad_perm<0x4e>(v);   // lanes 2, 3, 0, 1
+}
+
+// lanes that share a pair's blobs (a quad)
+constexpr int kDriftLanes = 4;
 
 // Drift of the id-ordered pair (a, b) of length len: sum_j (len/K)(1 - q(mid_j))
 // over the K sub-step midpoints x_a + ((j + 1/2)/K)(x_b - x_a), in float64
 // in j order from the float32 positions and length, rounded once to float32.
 //
 // Bound by float64 issue.  Along a segment a blob's exponent is quadratic in
-// j, so its values at successive midpoints follow from one exponential, the
-// ratio of the first two and the constant ratio of ratios: two exponentials
-// and three operations a midpoint instead of an exponential (about 45
-// operations) each.  A run of at most sixteen midpoints keeps the error of
-// the products below 2e-14 relative, far below the final rounding.  Where an
-// exponent is so large that the first value would underflow the run is
-// evaluated point by point, and blobs too far from all segments of the wave
-// to reach the last bit of q are left out.  L lanes share a pair's blobs when
-// there are too few pairs to fill the chip.  Every lane of the wave calls
-// (live: it holds a pair).
-template <int L, int D>
+// j, so its values at successive midpoints follow from the one at a run's
+// middle, the ratio to its neighbour on either side and the constant ratio of
+// ratios: three operations a midpoint instead of an exponential (about 45
+// operations) each.  The ratios are carried less one, so a step adds one
+// rounding of the value, and at most eight steps lie between a midpoint and
+// its run's middle.  Against 128-bit sums the mean relative error is 3.1e-16
+// (2D) and 4.2e-16 (3D) at the workloads' blobs, 5.3e-16 and 4.8e-16 with an
+// exponential a midpoint; where q is within 1e-7 of one, 1.6e-10 and 1.5e-10
+// (1.8e-10 and 1.4e-10).  A blob narrower than eight steps, or many widths
+// away, is evaluated point by point, and blobs too far from the segment to
+// reach the last bit of q are left out.
+//
+// What a lane adds depends on its pair alone (a wave leaves out what all its
+// lanes leave out) and the blobs are dealt out and summed in one way, so a
+// pair has the same drift in every roadmap with the same blobs.  Every lane
+// of the wave calls (live: it holds a pair).
+template <int D>
 __device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, float len,
                                             bool live) {
-    const int sub = lane_id() % L;
-    double xa[D], df[D];
+    const int sub = lane_id() % kDriftLanes;
+    double xa[D], df[D], dl[D], c2 = 0.0;  // dl: the step between midpoints, c2 its square
     float xaf[D];
+    int K = (int)ceilf(len / gl.step);
+    if (K < 1) K = 1;
+    const double dK = (double)K, rK = 1.0 / dK;
+    const double w = (double)len / dK;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         xaf[k] = gl.pos[a * D + k];
         xa[k] = (double)xaf[k];
         df[k] = (double)gl.pos[b * D + k] - xa[k];
-    }
-    int K = (int)ceilf(len / gl.step);
-    if (K < 1) K = 1;
-    const double dK = (double)K;
-    const double w = (double)len / dK;
-    // runs of equal length (a multiple of four) for the longest pair of the wave
-    const int kmax = __builtin_amdgcn_readfirstlane(wave_max_i(live ? K : 1));
-    const int runs = (kmax + kDriftRun - 1) / kDriftRun;
-    const int run = ((kmax + runs - 1) / runs + 3) & ~3;
-    double dl[D], c2 = 0.0;  // the step between midpoints and its square
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        dl[k] = df[k] / dK;
+        dl[k] = df[k] * rK;
         c2 = __builtin_fma(dl[k], dl[k], c2);
     }
+    // runs of equal length; the wave goes through those of its longest pair
+    const int runs = live ? (K - 1) / kDriftRun + 1 : 0;
+    const int run = live ? (K - 1) / runs + 1 : 0;
+    const int most = __builtin_amdgcn_readfirstlane(wave_max_i(runs));
+    const int longest = __builtin_amdgcn_readfirstlane(wave_max_i(run));
+    const int back = longest / 2, ahead = (longest - 1) / 2;  // steps from a run's middle
     // every point lies within len (and the roundings) of x_a
     const float reach = len * 1.0001f;
     double acc = 0.0;
-    for (int j0 = 0; j0 < kmax; j0 += run) {
+    for (int r = 0; r < most; ++r) {
+        const bool mine = r < runs;
+        const int j0 = r * run, jc = j0 + run / 2, j1 = min(j0 + run, K);
+        const double sc = ((double)jc + 0.5) / dK;
         double q[kDriftRun];
 #pragma unroll
         for (int i = 0; i < kDriftRun; ++i) q[i] = 0.0;
-        const double s0 = ((double)j0 + 0.5) / dK;
-        double x0[D];
-#pragma unroll
-        for (int k = 0; k < D; ++k) x0[k] = xa[k] + s0 * df[k];
-        for (int j = sub; j < gl.nblob; j += L) {
+        for (int j = sub; j < gl.nblob; j += kDriftLanes) {
             const float sg = gl.sig[j], am = gl.amp[j];
             float d2f = 0.0f, xs = 0.0f;
 #pragma unroll
@@ -192,59 +226,81 @@ __device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, f
             // far more than its roundings
             const float near = fmaxf(__builtin_amdgcn_sqrtf(d2f) * 0.9999f - reach - xs * 0x1p-20f, 0.0f);
             const float y = 0.7213f * __builtin_amdgcn_rcpf(sg * sg) * (near * near);
-            // (negated: NaN stays in)
-            if (ballot64(live && !(fabsf(am) * __builtin_amdgcn_exp2f(-y) < 0x1p-66f)) == 0) continue;
+            // (NaN and what float32 cannot hold stay in)
+            const bool in = mine && !(fabsf(am) * __builtin_amdgcn_exp2f(-y) < 0x1p-66f &&
+                                      d2f < MPAP_INF);
+            if (ballot64(in) == 0) continue;
             const double s = (double)sg, amp = (double)am;
+            const double two_s2 = 2.0 * (s * s);
             // 1 / (2 sigma^2) by two Newton steps (NaN where that fails: the
             // run is then evaluated point by point, with the division)
-            const double two_s2 = 2.0 * (s * s);
             double inv = __builtin_amdgcn_rcp(two_s2);
             inv = __builtin_fma(__builtin_fma(-two_s2, inv, 1.0), inv, inv);
             inv = __builtin_fma(__builtin_fma(-two_s2, inv, 1.0), inv, inv);
             double d2 = 0.0, g = 0.0;
 #pragma unroll
             for (int k = 0; k < D; ++k) {
-                const double t = x0[k] - (double)gl.mu[j * D + k];
+                const double t = __builtin_fma(sc, df[k], xa[k] - (double)gl.mu[j * D + k]);
                 d2 = __builtin_fma(t, t, d2);
                 g = __builtin_fma(t, dl[k], g);
             }
-            const double e0 = d2 * inv;                              // exponent at the first point
-            const double e1 = __builtin_fma(2.0, g, c2) * inv;       // to the second
-            const double e2 = 2.0 * c2 * inv;                        // and its growth
-            if (ballot64(live && !(e0 <= 690.0 && fabs(e1) <= 600.0 && e2 <= 0x1p-6)) == 0) {
-                double E = amp * exp(-e0), R = exp(-e1);
-                const double C = exp_small(e2);
+            // exponent at i steps from the middle: e + slope i + curve i^2
+            const double e = d2 * inv, slope = 2.0 * g * inv, curve = c2 * inv;
+            // (the run's least exponent is at least this)
+            const float least = 1.4425f * (float)(e - (double)kDriftMid * fabs(slope));
+            const bool near_run = in && !(fabsf(am) * __builtin_amdgcn_exp2f(-least) < 0x1p-66f);
+            const bool smooth = e <= 690.0 && fabs(slope) <= 2.0 && curve <= 0x1p-7 &&
+                                fabsf(am) < MPAP_INF;
+            if (ballot64(near_run && smooth)) {
+                const bool use = near_run && smooth;
+                double C, Rf, Rb;
+                // (the others add nothing)
+                expm1_both(use ? slope : 0.0, use ? curve : 0.0, Rf, Rb, C);
+                const double C1 = 1.0 + C;
+                double Ef = use ? amp * exp(-e) : 0.0, Eb = Ef;
+                q[kDriftMid] += Ef;
+                auto behind = [&](int i) {
+                    Eb = __builtin_fma(Eb, Rb, Eb);
+                    Rb = __builtin_fma(Rb, C1, C);
+                    q[kDriftMid - i] += Eb;
+                };
+                auto before = [&](int i) {
+                    Ef = __builtin_fma(Ef, Rf, Ef);
+                    Rf = __builtin_fma(Rf, C1, C);
+                    q[kDriftMid + i] += Ef;
+                };
 #pragma unroll
-                for (int i0 = 0; i0 < kDriftRun; i0 += 4)
-                    if (i0 < run) {
+                for (int i = 1; i <= kDriftMid; ++i) {
+                    if (i % 2 == 1 && longest < 2 * i) break;
+                    behind(i);
+                    if (i < kDriftMid) before(i);
+                }
+            }
+            if (ballot64(near_run && !smooth)) {
+                const bool use = near_run && !smooth;
+                int first = jc - kDriftMid;
+                asm volatile("" : "+v"(first));  // (no points kept from blob to blob: registers)
 #pragma unroll
-                        for (int i = i0; i < i0 + 4; ++i) {
-                            q[i] += E;
-                            E *= R;
-                            R *= C;
-                        }
-                    }
-            } else {
-                for (int i = 0; i < run; ++i) {
-                    const double si = ((double)(j0 + i) + 0.5) / dK;
+                for (int i = 0; i < kDriftRun; ++i) {
+                    if (i < kDriftMid - back || i > kDriftMid + ahead) continue;
+                    const double si = ((double)(first + i) + 0.5) / dK;
                     double t2 = 0.0;
 #pragma unroll
                     for (int k = 0; k < D; ++k) {
                         const double t = xa[k] + si * df[k] - (double)gl.mu[j * D + k];
                         t2 = t2 + t * t;
                     }
-                    const double v = amp * exp(-t2 / two_s2);
-#pragma unroll
-                    for (int k = 0; k < kDriftRun; ++k) q[k] += k == i ? v : 0.0;
+                    q[i] += use ? amp * exp(-t2 / two_s2) : 0.0;
+
                 }
             }
         }
 #pragma unroll
         for (int i = 0; i < kDriftRun; ++i) {
-            double v = q[i];
-#pragma unroll
-            for (int o = 1; o < L; o <<= 1) v += __shfl_xor(v, o, 64);
-            if (i < run && j0 + i < K) acc = acc + w * (1.0 - fmin(fmax(v, 0.0), 1.0));
+            if (i < kDriftMid - back || i > kDriftMid + ahead) continue;
+            const double v = quad_sum(q[i]);
+            const int j = jc + i - kDriftMid;
+            if (mine && j >= j0 && j < j1) acc = acc + w * (1.0 - fmin(fmax(v, 0.0), 1.0));
         }
     }
     return (float)acc;
@@ -601,30 +657,35 @@ __global__ void __launch_bounds__(256) k_row_ptr(int n, long long m, const int *
 }
 
 // The drift of every edge of a symmetric roadmap (rows sorted by target id,
-// the same value both ways), L lanes per id-ordered pair: the t-th pair's
-// value is evaluated once and written to both of its edges.  uptr[u] counts
-// the entries v > u of the rows before u (uptr[n] pairs in all).  Measured
-// against one thread per pair and an exponential per midpoint: 2,424 -> 474
-// us (3D, 50,000 samples, 80 blobs, 972,000 pairs) and 110 -> 17 us (2D,
-// 2,000 samples, 30 blobs, 21,000 pairs).  Three waves per SIMD: four spill
-// 49 registers (595 us).
-template <int L, int D>
+// the same value both ways), a quad of lanes per id-ordered pair: the t-th
+// pair's value is evaluated once and written to both of its edges.  uptr[u]
+// counts the entries v > u of the rows before u (uptr[n] pairs in all).
+// Measured against one thread per pair and an exponential per midpoint:
+// 2,164 -> 548 us (3D, 50,000 samples, 80 blobs, 968,000 pairs), 1,113 -> 229
+// (368,000 pairs), 860 -> 115 (82,000 pairs) and 109 -> 16 (2D, 2,000
+// samples, 30 blobs, 21,000 pairs); widths of 0.01 to 0.03, most runs point by
+// point, 1,107 -> 568 (3D, 12,000 samples).  One number of lanes for all sizes,
+// since it fixes the order of the sums; with 1 / 2 / 4 / 8 lanes: 3D, 9,000
+// pairs 151 / 84 / 49 / 41 us; 82,000 pairs 157 / 116 / 115 / 120; 968,000
+// pairs 500 / 522 / 553 / 654; 2D, 21,000 pairs 26 / 17 / 16 / 16; 601,000
+// pairs 128 / 134 / 165 / 221.
+template <int D>
 __global__ void __launch_bounds__(256, 3) k_edge_drift_pairs(BuildArgs g, int n, const int *row_ptr,
                                                           const int *col, const float *cost,
                                                           const int *uptr, float *drift) {
     extern __shared__ float blob[];
     const BuildArgs gl = stage_blobs(g, blob);
     const int pairs = uptr[n];
-    const int i = (int)((blockIdx.x * 256ll + threadIdx.x) / L);
+    const int i = (int)((blockIdx.x * 256ll + threadIdx.x) / kDriftLanes);
     // (whole waves: the lanes beyond the last pair repeat it)
-    if ((int)((blockIdx.x * 256ll + (threadIdx.x & ~63)) / L) >= pairs) return;
+    if ((int)((blockIdx.x * 256ll + (threadIdx.x & ~63)) / kDriftLanes) >= pairs) return;
     const bool live = i < pairs;
     const int t = min(i, pairs - 1);
     const int u = wave_pair_row(uptr, n, t);
     const int e = row_ptr[u + 1] - (uptr[u + 1] - t);
     const int v = col[e];
-    const float d = pair_drift<L, D>(gl, u, v, cost[e], live);
-    if (!live || lane_id() % L) return;
+    const float d = pair_drift<D>(gl, u, v, cost[e], live);
+    if (!live || lane_id() % kDriftLanes) return;
     drift[e] = d;
     const int r = reverse_edge(row_ptr, col, v, u);
     if (r >= 0) drift[r] = d;
@@ -935,28 +996,12 @@ void launch_edge_features(const BuildArgs &g, bool plain, int n, long long pairs
         edge_features<false, 3>(g, n, pairs, row_ptr, col, cost, uptr, node_w, X, base, s);
 }
 
-template <int D>
-static void drift_pairs(const BuildArgs &g, int n, long long pairs, const int *row_ptr,
-                        const int *col, const float *cost, const int *uptr, float *drift,
-                        hipStream_t s) {
-    const size_t lds = sizeof(float) * ((size_t)g.nblob * D + 2 * (size_t)g.nblob);
-    auto blocks = [&](int lanes) { return (unsigned)((pairs * lanes + 255) / 256); };
-    if (pairs <= 32768)
-        k_edge_drift_pairs<8, D><<<blocks(8), 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
-    else if (pairs <= 131072)
-        k_edge_drift_pairs<2, D><<<blocks(2), 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
-    else
-        k_edge_drift_pairs<1, D><<<blocks(1), 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
-}
-
-// pairs: uptr[n] (half the edges).  Lanes per pair until the chip is full;
-// beyond that the per-pair work that every lane repeats costs more.  Measured
-// with 1 / 2 / 8 lanes: 3D, 5,900 pairs 197 / 104 / 40 us; 30,000 pairs 151 /
-// 85 / 69; 83,000 pairs 154 / 116 / 119; 177,000 pairs 206 / 201 / 214;
-// 2D, 114,000 pairs 34 / 35 / 51; 592,000 pairs 119 / 128 / 237.
+// pairs: uptr[n] (half the edges)
 void launch_edge_drift_pairs(const BuildArgs &g, int n, long long pairs, const int *row_ptr,
                              const int *col, const float *cost, const int *uptr, float *drift,
                              hipStream_t s) {
-    if (g.dim == 2) drift_pairs<2>(g, n, pairs, row_ptr, col, cost, uptr, drift, s);
-    else drift_pairs<3>(g, n, pairs, row_ptr, col, cost, uptr, drift, s);
+    const size_t lds = sizeof(float) * ((size_t)g.nblob * g.dim + 2 * (size_t)g.nblob);
+    const unsigned blocks = (unsigned)((pairs * kDriftLanes + 255) / 256);
+    if (g.dim == 2) k_edge_drift_pairs<2><<<blocks, 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
+    else k_edge_drift_pairs<3><<<blocks, 256, lds, s>>>(g, n, row_ptr, col, cost, uptr, drift);
 }

@@ -9,6 +9,8 @@
   objectives, the 20,000-sample 3D workload), and on small graphs whose edges
   get dearer, cheaper, removed or added and whose relocalisation flags flip.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -52,6 +54,46 @@ def test_added_boxes_give_the_rebuilt_roadmap(name, make, nbox):
     assert_same_graph(got, fresh.export(), (name, "library build"))
     assert_same_graph(got, ograph.build_graph(env2), (name, "oracle build"))
     assert g1.info()["e"] < g0.info()["e"]
+    for g in (g0, g1, fresh):
+        g.close()
+
+
+def near_one(env, seed):
+    """env with eight blobs so wide that the quality is 1 - 2^-23 and a little
+    less everywhere: 1 - q, a few 1e-7 wide, shows single roundings of the
+    float64 sums behind the drift."""
+    rng = np.random.default_rng(seed)
+    amp = np.full(8, 0.125, np.float32)
+    amp[5] = np.float32(0.125 - 2.0 ** -23)
+    return dataclasses.replace(env, blob_mu=rng.random((8, env.dim)).astype(np.float32),
+                               blob_sigma=np.full(8, 1e4, np.float32), blob_amp=amp)
+
+
+@pytest.mark.parametrize("dim,n", [(2, 400), (2, 2000), (3, 5000), (3, 12000)])
+def test_a_pairs_drift_does_not_depend_on_the_roadmap_around_it(dim, n):
+    """Roadmaps from 4,000 to 200,000 pairs: every edge left after boxes were
+    added has the drift bits of a fresh build of the changed map, and on the
+    smaller ones (the oracle's midpoints are one exponential each) the drift is
+    that of the oracle but for roundings.  The float64 mean of 1 - q is off by
+    at most 3e-16 on either side, and float32 values of it (above 2^-23) lie
+    2^-47 = 7e-15 or more apart: at most one of them between the two, and that
+    for less than 2 * 3e-16 / 7e-15, a tenth, at the very worst; a typical error
+    is a twentieth of that, so one percent."""
+    env = near_one(synth.plain2d(5, n=n) if dim == 2 else synth.plain3d(5, n=n), dim)
+    env = dataclasses.replace(env, goal=env.pos[-1].copy())
+    lo, hi = synth.discovered_boxes(env, 1, 5)
+    g0 = mpap.mpap_build_graph(env)
+    g1 = mpap.mpap_graph_add_boxes(g0, lo, hi)
+    fresh = mpap.mpap_build_graph(synth.with_boxes(env, lo, hi))
+    assert g1.info()["e"] < g0.info()["e"]
+    assert_same_graph(g1.export(), fresh.export(), (dim, n))
+    if n <= 2000:
+        got, want = g0.export(), ograph.build_graph(env)
+        assert np.array_equal(got["col"], want["col"])
+        ulps = np.abs(bits(got["drift"]).astype(np.int64) - bits(want["drift"]).astype(np.int64))
+        print(f"{dim}D n={n}: {int((ulps > 0).sum())} of {ulps.size} differ", flush=True)
+        assert ulps.max() <= 1
+        assert (ulps > 0).sum() <= 0.01 * ulps.size
     for g in (g0, g1, fresh):
         g.close()
 
