@@ -223,12 +223,13 @@ __device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, f
                 xs += fabsf(xaf[k]) + fabsf(mu);
             }
             // exponent (base 2) at the nearest the segment can come, low by
-            // far more than its roundings
-            const float near = fmaxf(__builtin_amdgcn_sqrtf(d2f) * 0.9999f - reach - xs * 0x1p-20f, 0.0f);
+            // far more than its roundings, against the one whose value is
+            // below 2^-66 (NaN and what float32 cannot hold stay in)
+            const float gap = __builtin_amdgcn_sqrtf(d2f) * 0.9999f - reach - xs * 0x1p-20f;
+            const float near = gap < 0.0f ? 0.0f : gap;
             const float y = 0.7213f * __builtin_amdgcn_rcpf(sg * sg) * (near * near);
-            // (NaN and what float32 cannot hold stay in)
-            const bool in = mine && !(fabsf(am) * __builtin_amdgcn_exp2f(-y) < 0x1p-66f &&
-                                      d2f < MPAP_INF);
+            const float end = 66.0f + __builtin_amdgcn_logf(fabsf(am));
+            const bool in = mine && !(y > end && d2f < MPAP_INF);
             if (ballot64(in) == 0) continue;
             const double s = (double)sg, amp = (double)am;
             const double two_s2 = 2.0 * (s * s);
@@ -248,7 +249,7 @@ __device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, f
             const double e = d2 * inv, slope = 2.0 * g * inv, curve = c2 * inv;
             // (the run's least exponent is at least this)
             const float least = 1.4425f * (float)(e - (double)kDriftMid * fabs(slope));
-            const bool near_run = in && !(fabsf(am) * __builtin_amdgcn_exp2f(-least) < 0x1p-66f);
+            const bool near_run = in && !(least > end);
             const bool smooth = e <= 690.0 && fabs(slope) <= 2.0 && curve <= 0x1p-7 &&
                                 fabsf(am) < MPAP_INF;
             if (ballot64(near_run && smooth)) {

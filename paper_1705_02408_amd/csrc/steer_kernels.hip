@@ -1037,14 +1037,14 @@ __global__ void __launch_bounds__(256) k_traj_drift(SteerArgs a, const SteerBlob
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
                     const float m = a.mu[3 * j + d];
-                    const float t = fmaxf(fmaxf(lo[d] - m, m - hi[d]), 0.0f);
-                    d2 = __builtin_fmaf(t, t, d2);
+                    const float t = fmaxf(lo[d] - m, m - hi[d]);
+                    if (!(t <= 0.0f)) d2 = __builtin_fmaf(t, t, d2);
                 }
                 const float sg = a.sig[j];
-                // (negated: NaN stays in)
-                keep = !(fabsf(a.amp[j]) *
-                             __builtin_amdgcn_exp2f(-0.7213f * d2 * __builtin_amdgcn_rcpf(sg * sg)) <
-                         0x1p-66f);
+                // base-two exponent at the hull, against the one whose value
+                // is below 2^-66 (NaN and what float32 cannot hold stay in)
+                const float y = 0.7213f * d2 * __builtin_amdgcn_rcpf(sg * sg);
+                keep = !(y > 66.0f + __builtin_amdgcn_logf(fabsf(a.amp[j])) && d2 < MPAP_INF);
             }
             const uint64_t m = ballot64(keep);
             if (l == 0) mask[g] = m;

@@ -6,7 +6,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from oracle import graph6d, mlp, search as osearch
+from oracle import graph as ograph, graph6d, mlp, search as osearch
 from paper_1705_02408_amd import synth
 from tests.test_gpu_search import bits, check_against_oracle
 
@@ -162,6 +162,27 @@ def test_surrogate_on_6d_edges(built):
     assert not rejected
     res.close()
     s.close()
+
+
+@pytest.mark.parametrize("dim,amp", [(2, 3e38), (3, 3e38), (6, 3e38), (6, -3e38), (3, 1e-45), (6, 0.0)])
+def test_a_blob_of_extreme_amplitude(dim, amp):
+    """A narrow blob alone, of nearly the largest float32 amplitude: it
+    saturates the quality out to 13 widths and has an effect to 16, where the
+    float32 exponential is zero; one that subtracts as much, of the least
+    amplitude and of none.  Every drift and flag as the oracle's."""
+    env = synth.plain6d(7, n=1200) if dim == 6 else (
+        synth.plain2d(7, n=500) if dim == 2 else synth.plain3d(7, n=500))
+    env = dataclasses.replace(
+        env, blob_mu=env.blob_mu[3:4], blob_sigma=np.full(1, 0.02, np.float32),
+        blob_amp=np.full(1, amp, np.float32), goal=env.pos[-1][:min(dim, 3)].copy(),
+        goal_radius=0.2)
+    ref = graph6d.build_graph6d(env) if dim == 6 else ograph.build_graph(env)
+    dg = mpap.mpap_build_graph(env)
+    got = dg.export()
+    dg.close()
+    for k in ("row_ptr", "col", "reset"):
+        assert np.array_equal(got[k], ref[k]), k
+    assert np.array_equal(bits(got["drift"]), bits(ref["drift"]))
 
 
 @pytest.mark.parametrize("n,k_out,cluster", [(2, 24, False), (66, 64, False), (900, 5, True),
