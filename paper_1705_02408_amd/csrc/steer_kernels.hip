@@ -920,16 +920,20 @@ __global__ void __launch_bounds__(256) k_steer_compact(int n, int k_out, const i
 
 namespace {
 
+// From here on the exponential counts as zero (e^-700 is 1e-304); and where
+// the plain one becomes zero.
+constexpr double kExpEnd = 700.0, kExpZero = 745.1332191019412;
+
 // exp(-x), x >= 0, by table: -x = k ln 2 / 64 + r, |r| <= ln 2 / 128, so
 // exp(-x) = 2^(k div 64) 2^((k mod 64)/64) e^r, with e^r - 1 by its series to
 // r^5 (the next term is below 2^-55 of the result) (Tang, "Table-driven
 // implementation of the exponential function in IEEE floating-point
 // arithmetic", ACM TOMS 15, 1989).  pow[j] = 2^(j/64).  k is rounded by
 // adding 1.5 2^52, whose low word then holds it; its power of two goes
-// into the table entry's exponent.  From x = 700 on the result is e^-700.
-// Off by at most 2.2e-16 of the result (2 million points).
+// into the table entry's exponent.  Zero beyond kExpEnd (where the exponent
+// would leave its range), NaN for NaN.  Off by at most 2.2e-16 of the result
+// (2 million points).
 __device__ __forceinline__ double exp_neg(double x, const double *pow) {
-    x = fmin(x, 700.0);
     const double big = 6755399441055744.0;
     const double kb = __builtin_fma(x, -92.33248261689366, big);
     const int k = __double2loint(kb);
@@ -943,7 +947,7 @@ __device__ __forceinline__ double exp_neg(double x, const double *pow) {
     p = __builtin_fma(r, p, 1.0 / 6.0);
     p = __builtin_fma(r, p, 0.5);
     p = __builtin_fma(r * r, p, r);
-    return __builtin_fma(t, p, t);
+    return x > kExpEnd ? 0.0 : __builtin_fma(t, p, t);
 }
 
 }  // namespace
@@ -960,6 +964,9 @@ __global__ void __launch_bounds__(256) k_steer_blobs(int nblob, const float *mu,
     for (int d = 0; d < 3; ++d) b.mu[d] = (double)mu[3 * j + d];
     b.inv = 1.0 / (2.0 * (s * s));
     b.amp = (double)amp[j];
+    // an infinite amplitude counts at every point whose plain exponential is
+    // not zero, and gives NaN (so q = 0) elsewhere: only where it ends matters
+    if (isinf(amp[j])) b.inv *= kExpEnd / kExpZero;
     out[j] = b;
 }
 

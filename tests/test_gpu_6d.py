@@ -185,6 +185,45 @@ def test_a_blob_of_extreme_amplitude(dim, amp):
     assert np.array_equal(bits(got["drift"]), bits(ref["drift"]))
 
 
+@pytest.mark.parametrize("what", ["NaN centre", "NaN amplitude", "infinite amplitude",
+                                  "infinite amplitude, narrow", "minus infinite amplitude",
+                                  "infinite centre", "infinite width"])
+@pytest.mark.parametrize("dim", [2, 3, 6])
+def test_blobs_that_are_not_finite(dim, what, monkeypatch):
+    """A map with a blob of NaN or infinite values: the drift and the
+    relocalisation flags are those of the plain sum, a NaN sum counting as
+    q = 0 (an infinite amplitude times an exponential that has become zero is
+    NaN, too)."""
+    for mod in (graph6d, ograph):
+        plain = mod.quality
+        monkeypatch.setattr(mod, "quality", lambda *a, plain=plain: np.nan_to_num(plain(*a)))
+    env = synth.plain6d(7, n=300) if dim == 6 else (
+        synth.plain2d(7, n=300) if dim == 2 else synth.plain3d(7, n=300))
+    mu, sig, amp = env.blob_mu.copy(), env.blob_sigma.copy(), env.blob_amp.copy()
+    j = 5
+    if what == "NaN centre":
+        mu[j, 1] = np.nan
+    elif what == "NaN amplitude":
+        amp[j] = np.nan
+    elif what == "infinite centre":
+        mu[j, 0] = np.inf
+    elif what == "infinite width":
+        sig[j] = np.inf
+    else:
+        amp[j] = -np.inf if "minus" in what else np.inf
+        sig[j] = 0.02 if "narrow" in what else 0.1
+    env = dataclasses.replace(env, blob_mu=mu, blob_sigma=sig, blob_amp=amp,
+                              goal=env.pos[-1][:min(dim, 3)].copy(), goal_radius=0.2)
+    with np.errstate(all="ignore"):
+        ref = graph6d.build_graph6d(env) if dim == 6 else ograph.build_graph(env)
+    dg = mpap.mpap_build_graph(env)
+    got = dg.export()
+    dg.close()
+    for k in ("row_ptr", "col", "reset"):
+        assert np.array_equal(got[k], ref[k]), k
+    assert np.array_equal(bits(got["drift"]), bits(ref["drift"]))
+
+
 @pytest.mark.parametrize("n,k_out,cluster", [(2, 24, False), (66, 64, False), (900, 5, True),
                                              (900, 24, True)])
 def test_in_edges_of_the_device_build(n, k_out, cluster):
