@@ -72,9 +72,10 @@ __global__ void k_steer_select(SteerArgs a, const int *left, const int *nleft, i
 // rows of the CSR, each sorted by target id
 __global__ void k_steer_compact(int n, int k_out, const int *row_ptr, const int *nbr,
                                 const float *ncost, const int *ncnt, int *col, float *cost);
-// a blob widened to float64: centre, 1 / (2 sigma^2), amplitude
+// a blob widened to float64: centre, 1 / (2 sigma^2), amplitude, and the
+// exponent beyond which its value counts as zero (below 2^-65)
 struct SteerBlob {
-    double mu[3], inv, amp, pad[3];
+    double mu[3], inv, amp, end, pad[2];
 };
 __global__ void k_steer_blobs(int nblob, const float *mu, const float *sig, const float *amp,
                               SteerBlob *out);

@@ -930,10 +930,10 @@ constexpr double kExpEnd = 700.0, kExpZero = 745.1332191019412;
 // implementation of the exponential function in IEEE floating-point
 // arithmetic", ACM TOMS 15, 1989).  pow[j] = 2^(j/64).  k is rounded by
 // adding 1.5 2^52, whose low word then holds it; its power of two goes
-// into the table entry's exponent.  Zero beyond kExpEnd (where the exponent
-// would leave its range), NaN for NaN.  Off by at most 2.2e-16 of the result
-// (2 million points).
-__device__ __forceinline__ double exp_neg(double x, const double *pow) {
+// into the table entry's exponent.  Zero beyond `end` (at most kExpEnd: there
+// the exponent would leave its range), NaN for NaN.  Off by at most 2.2e-16 of
+// the result (2 million points).
+__device__ __forceinline__ double exp_neg(double x, double end, const double *pow) {
     const double big = 6755399441055744.0;
     const double kb = __builtin_fma(x, -92.33248261689366, big);
     const int k = __double2loint(kb);
@@ -947,7 +947,7 @@ __device__ __forceinline__ double exp_neg(double x, const double *pow) {
     p = __builtin_fma(r, p, 1.0 / 6.0);
     p = __builtin_fma(r, p, 0.5);
     p = __builtin_fma(r * r, p, r);
-    return x > kExpEnd ? 0.0 : __builtin_fma(t, p, t);
+    return x > end ? 0.0 : __builtin_fma(t, p, t);
 }
 
 }  // namespace
@@ -967,6 +967,7 @@ __global__ void __launch_bounds__(256) k_steer_blobs(int nblob, const float *mu,
     // an infinite amplitude counts at every point whose plain exponential is
     // not zero, and gives NaN (so q = 0) elsewhere: only where it ends matters
     if (isinf(amp[j])) b.inv *= kExpEnd / kExpZero;
+    b.end = fmin(kExpEnd, log(fabs(b.amp)) + 65.0 * 0.6931471805599453);
     out[j] = b;
 }
 
@@ -980,7 +981,8 @@ __global__ void __launch_bounds__(256) k_steer_blobs(int nblob, const float *mu,
 // terms in LDS and summed by one lane per edge.  Bound by the float64
 // exponential of each chord and blob: blobs whose centre is too far from the
 // hull of the edges' Bezier control points to reach the last bit of q are
-// left out, the exponent is scaled by 1 / (2 sigma^2) instead of divided, the
+// left out (a value below 2^-66; each lane drops those below 2^-65 itself, so
+// an edge's drift does not depend on the edges beside it), the exponent is scaled by 1 / (2 sigma^2) instead of divided, the
 // exponential is exp_neg, and the blobs, the same for the whole wave, come
 // through scalar loads four at a time.  Measured, 20,000 states (100 blobs,
 // 569,000 edges): 5.6 ms (14.2 ms with one edge at a time and the general
@@ -1105,7 +1107,7 @@ __global__ void __launch_bounds__(256) k_traj_drift(SteerArgs a, const SteerBlob
                             const double t = mid[d] - blob[j[i]].mu[d];
                             d2 = __builtin_fma(t, t, d2);
                         }
-                        e[i] = exp_neg(d2 * blob[j[i]].inv, pow);
+                        e[i] = exp_neg(d2 * blob[j[i]].inv, blob[j[i]].end, pow);
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i)

@@ -224,6 +224,42 @@ def test_blobs_that_are_not_finite(dim, what, monkeypatch):
     assert np.array_equal(bits(got["drift"]), bits(ref["drift"]))
 
 
+def test_an_edges_drift_does_not_depend_on_its_row():
+    """The same states with five and with thirty edges each: an edge that is
+    in both roadmaps has the same drift bits.  States around 8,000 blobs in
+    one place, at the distances where these end to count, and then eight blobs
+    so wide that q is 1 - 2^-27 everywhere, so that single roundings of its sum
+    show in the drift."""
+    env = synth.plain6d(3, n=3000)
+    rng = np.random.default_rng(1)
+    away = rng.standard_normal((3001, 3))
+    away *= rng.uniform(0.29, 0.33, (3001, 1)) / np.linalg.norm(away, axis=1, keepdims=True)
+    m = 8000
+    mu = np.full((m + 8, 3), 0.5, np.float32)
+    amp = np.full(m + 8, 2.0 ** -40, np.float32)
+    amp[m:] = 0.125
+    amp[m + 5] = np.float32(0.125 - 2.0 ** -27)
+    sigma = np.full(m + 8, 0.05, np.float32)
+    sigma[m:] = 1e6
+    env = dataclasses.replace(env, pos=(0.5 + away).astype(np.float32), vel=env.vel * np.float32(0.05),
+                              traj_steps=3, blob_mu=mu, blob_sigma=sigma, blob_amp=amp,
+                              box_lo=env.box_lo[:0], box_hi=env.box_hi[:0])
+    env = dataclasses.replace(env, goal=env.pos[-1].copy())
+    drift = []
+    for k_out in (5, 30):
+        e = dataclasses.replace(env, k_out=k_out)
+        dg = mpap.mpap_build_graph(e)
+        got = dg.export()
+        dg.close()
+        src = np.repeat(np.arange(got["row_ptr"].size - 1, dtype=np.int64), np.diff(got["row_ptr"]))
+        drift.append(dict(zip((src * 10000 + got["col"]).tolist(), bits(got["drift"]).tolist())))
+    both = drift[0].keys() & drift[1].keys()
+    assert 5 * 2500 < len(both) == len(drift[0])
+    differ = sum(drift[0][k] != drift[1][k] for k in both)
+    print(f"{differ} of {len(both)} edges in both differ", flush=True)
+    assert differ == 0
+
+
 @pytest.mark.parametrize("n,k_out,cluster", [(2, 24, False), (66, 64, False), (900, 5, True),
                                              (900, 24, True)])
 def test_in_edges_of_the_device_build(n, k_out, cluster):
