@@ -284,24 +284,26 @@ __device__ __forceinline__ float dist2(const float (&x)[D], const float (&mu)[D]
 
 // The quality q(x) in float64, the blobs shared by the flight's lanes.  Four
 // blobs a step, so that their exponentials overlap; a step whose terms are
-// all below `drop` (far below the last bit of any q that counts) for every
-// flight of the wave is left out.
+// all below 2^-end (far below the last bit of any q that counts) for every
+// flight of the wave is left out (never for a NaN or a distance that float32
+// cannot hold).
 template <int G, int D>
 __device__ __forceinline__ double quality(const double (&x)[D], const float (&xf)[D], int sub,
-                                          const BlobLds<D> &bl, const double *inv2s, float drop) {
+                                          const BlobLds<D> &bl, const double *inv2s, float end) {
     double acc = 0.0;
     for (int j0 = sub; j0 < bl.n; j0 += 4 * G) {
-        float mu[4][D], amp[4], most = 0.0f;
+        float mu[4][D], amp[4];
+        bool counts = false;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int j = j0 + i * G;
             float sc;
             bl.get(min(j, bl.n - 1), mu[i], sc, amp[i]);
             if (j >= bl.n) amp[i] = 0.0f;
-            const float term = fabsf(amp[i]) * __builtin_amdgcn_exp2f(-(dist2<D>(xf, mu[i]) * sc));
-            most = term <= most ? most : term;  // (NaN is kept)
+            const float d2 = dist2<D>(xf, mu[i]);
+            counts = counts || !(d2 * sc > end + __builtin_amdgcn_logf(fabsf(amp[i])) && d2 < MPAP_INF);
         }
-        if (ballot64(!(most < drop)) == 0) continue;
+        if (ballot64(counts) == 0) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             double d2 = 0.0;
@@ -373,7 +375,10 @@ __global__ void __launch_bounds__(256, 2) k_mc_rollout(McArgs a) {
     m1 = (wmarg[0][1] + wmarg[1][1]) + (wmarg[2][1] + wmarg[3][1]);
     // q < qmin follows from the sum alone only for a positive qmin
     const float qcut = a.qmin > 0.0 ? (float)a.qmin : -MPAP_INF;
-    const float drop = a.qmin > 0.0 ? (float)a.qmin * 0x1p-62f / (float)max(a.nblob, 1) : 0.0f;
+    // terms below 2^-62 qmin / nblob do not count
+    const float end = a.qmin > 0.0 ? 62.0f + __builtin_amdgcn_logf((float)max(a.nblob, 1)) -
+                                         __builtin_amdgcn_logf((float)a.qmin)
+                                   : MPAP_INF;
 
     constexpr int kCalls = (3 * D + 1) / 2;     // Philox calls of a step
     constexpr int kAll = (kCalls + G - 1) / G;  // rounds of them, one call per lane
@@ -491,7 +496,7 @@ __global__ void __launch_bounds__(256, 2) k_mc_rollout(McArgs a) {
             fq = flight_sum<G>(fq);
             const bool maybe = live && !(fq + marg < qcut);
             if (ballot64(maybe)) {
-                const double q = quality<G, D>(p, xf, sub, bl, a.inv2s, drop);
+                const double q = quality<G, D>(p, xf, sub, bl, a.inv2s, end);
                 const bool fix = maybe && q >= a.qmin;
                 if (ballot64(fix)) {
                     draw((uint32_t)k, kMove, kAll);

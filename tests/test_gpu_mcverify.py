@@ -156,6 +156,46 @@ def test_mc_every_lane_split(rollouts, case):
     assert st["within_bound"] == int((got <= mp.f64("err_bound")).sum())
 
 
+@pytest.mark.parametrize("rollouts", [256, 65537])
+@pytest.mark.parametrize("what", ["NaN centre", "NaN amplitude", "infinite amplitude",
+                                  "huge amplitude", "huge amplitudes of both signs"])
+def test_mc_fixes_beside_an_odd_blob(rollouts, what, monkeypatch):
+    """The blobs that a position fix may leave out, four at a time: not those
+    that make the sum NaN (which counts as q = 0: no fix), and not narrow ones
+    of nearly the largest float32 amplitude, which count out to 16 widths
+    where their float32 exponential is zero.  The first four blobs are the odd
+    ones and others far away; a flight over sixteen lanes and on one.  Same
+    tolerance as compare()."""
+    plain = mc.quality
+    monkeypatch.setattr(mc, "quality", lambda *a: np.nan_to_num(plain(*a)))
+    env = synth.plain2d(3, n=400) if rollouts > 256 else synth.plain3d(3, n=400)
+    path = np.array([0, 7, 11, 5], np.int32)
+    mu, sigma, amp = env.blob_mu.copy(), env.blob_sigma.copy(), env.blob_amp.copy()
+    mu[:4] += np.float32(50.0)
+    if what == "NaN centre":
+        mu[0, 0] = np.nan
+    elif what == "NaN amplitude":
+        amp[1] = np.nan
+    else:
+        mu[0], sigma[0], amp[0] = env.pos[7], 0.02, np.inf if what.startswith("inf") else 3e38
+        if "both" in what:
+            mu[1], sigma[1], amp[1] = env.pos[7] + np.float32(0.01), 0.02, -3e38
+    env = dataclasses.replace(env, blob_mu=mu, blob_sigma=sigma, blob_amp=amp, goal_radius=0.4)
+    kw = dict(rollouts=rollouts, dt=0.01, speed=2.0, q_min=0.3)
+    mp = mc.MCParams(**kw)
+    p, v, a = mc.nominal_segments(env.pos[path], mp.f64("speed"), mp.f64("dt"))
+    ids = np.arange(0, rollouts, max(1, rollouts // 256))
+    with np.errstate(all="ignore"):
+        want = mc.rollouts(p, v, a, mp, env.blob_mu, env.blob_sigma, env.blob_amp, env.box_lo,
+                           env.box_hi, rollout_ids=ids)
+    dg = mpap.mpap_build_graph(env)
+    st, got, col = mpap.mpap_mc_verify(dg, path, **kw)
+    dg.close()
+    rel = np.abs(got[ids] - want.max_err) / np.maximum(want.max_err, 1e-300)
+    assert rel.max() <= 1e-9, (rel.max(), int(ids[rel.argmax()]))
+    assert np.array_equal(col[ids], want.collided)
+
+
 def test_lower_drift_plans_fly_with_smaller_errors():
     """The perception heuristic against the estimate: over the goal front of
     the 20,000-sample 3D workload, the mean largest localisation error of a
