@@ -425,7 +425,8 @@ __global__ void __launch_bounds__(256, 2) k_mc_rollout(McArgs a) {
     float at[D];            // where the box list and the last bound were taken
     bool holds = false;     // the bound rules out a fix within roam of there
     uint64_t near0 = 0, near1 = 0;  // boxes sub + i G within roam of there, i < 128
-    const float roam = (float)a.roam, roam2 = 0.98f * roam * roam;
+    // (finite, so that every flight is beyond it at first)
+    const float roam = (float)a.roam, roam2 = fminf(0.98f * roam * roam, __FLT_MAX__);
 #pragma unroll
     for (int c = 0; c < D; ++c) at[c] = MPAP_INF;
     for (int k = 0; k < a.nm.K; ++k) {

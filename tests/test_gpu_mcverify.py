@@ -196,6 +196,27 @@ def test_mc_fixes_beside_an_odd_blob(rollouts, what, monkeypatch):
     assert np.array_equal(col[ids], want.collided)
 
 
+@pytest.mark.parametrize("speed", [1e18, 3e18, 1e20, 3e38])
+def test_mc_boxes_at_extreme_speed(speed):
+    """Peak speeds whose eight steps (the distance within which a list of
+    boxes holds) have a square beyond float32, or are beyond it themselves:
+    flights of one step that noise of the size of space itself carries to
+    either side, half of them into a box that takes up all of one."""
+    env = synth.plain2d(3, n=400)
+    lo, hi = np.float32([[0.5, -3e38]]), np.float32([[3e38, 3e38]])
+    env = dataclasses.replace(env, goal_radius=0.4, box_lo=lo, box_hi=hi)
+    path = np.array([0, 7, 11, 5], np.int32)
+    kw = dict(rollouts=512, dt=0.05, speed=speed, sigma_w=1e30)
+    mp = mc.MCParams(**kw)
+    p, v, a = mc.nominal_segments(env.pos[path], mp.f64("speed"), mp.f64("dt"))
+    want = mc.rollouts(p, v, a, mp, env.blob_mu, env.blob_sigma, env.blob_amp, lo, hi)
+    dg = mpap.mpap_build_graph(env)
+    st, _, col = mpap.mpap_mc_verify(dg, path, **kw)
+    dg.close()
+    assert st["steps"] == 1 and 128 < want.collided.sum() < 384
+    assert np.array_equal(col, want.collided)
+
+
 def test_lower_drift_plans_fly_with_smaller_errors():
     """The perception heuristic against the estimate: over the goal front of
     the 20,000-sample 3D workload, the mean largest localisation error of a
