@@ -346,33 +346,30 @@ __global__ void __launch_bounds__(256, 2) k_mc_rollout(McArgs a) {
     extern __shared__ __align__(16) float env[];  // blobs (D + 2 words each), box lo, box hi
     const BlobLds<D> bl{env, a.nblob};
     float *blo = env + a.nblob * (D + 2), *bhi = blo + a.nbox * D;
-    __shared__ float wmarg[4][2];
-    float m0 = 0.0f, m1 = 0.0f;
     for (int i = threadIdx.x; i < a.nblob; i += blockDim.x) {
-        const float amp = a.amp[i];
         const double scale = 0.8493218002880191 / (double)a.sig[i];  // sqrt(log2(e) / 2) / sigma
-        bl.put(i, a.mu + i * D, (float)(scale * scale), amp);
+        bl.put(i, a.mu + i * D, (float)(scale * scale), a.amp[i]);
+    }
+    for (int i = threadIdx.x; i < a.nbox * D; i += blockDim.x) {
+        blo[i] = a.blo[i];
+        bhi[i] = a.bhi[i];
+    }
+    __syncthreads();
+    // (by every wave for itself: all the LDS is the blobs' and boxes')
+    float m0 = 0.0f, m1 = 0.0f;
+    for (int i = lane_id(); i < a.nblob; i += 64) {
+        float mu[D], sc, amp;
+        bl.get(i, mu, sc, amp);
         // Error of one float32 term 2^-y, y = scale^2 |x - mu|^2: x rounds by
         // 2^-24 |x|, so y is off by 2 sqrt(y) scale |x| 2^-24 + 10 y 2^-24
         // and the term by ln 2 times that (at most 0.72 scale |x| + 4 units
         // of 2^-24) and by 2^-22 of the exponential itself: 0.72 scale |x| +
         // 8 units, and nblob units for the sum.  Twice that is taken.
         m0 += fabsf(amp) * (16.0f + 2.0f * (float)a.nblob) * 0x1p-24f;
-        m1 += fabsf(amp) * 2.0f * (float)scale * 0x1p-24f;
-    }
-    for (int i = threadIdx.x; i < a.nbox * D; i += blockDim.x) {
-        blo[i] = a.blo[i];
-        bhi[i] = a.bhi[i];
+        m1 += fabsf(amp) * 2.0f * __builtin_amdgcn_sqrtf(sc) * 0x1p-24f;
     }
     m0 = wave_sum(m0);
     m1 = wave_sum(m1);
-    if (lane_id() == 0) {
-        wmarg[threadIdx.x >> 6][0] = m0;
-        wmarg[threadIdx.x >> 6][1] = m1;
-    }
-    __syncthreads();
-    m0 = (wmarg[0][0] + wmarg[1][0]) + (wmarg[2][0] + wmarg[3][0]);
-    m1 = (wmarg[0][1] + wmarg[1][1]) + (wmarg[2][1] + wmarg[3][1]);
     // q < qmin follows from the sum alone only for a positive qmin
     const float qcut = a.qmin > 0.0 ? (float)a.qmin : -MPAP_INF;
     // terms below 2^-62 qmin / nblob do not count

@@ -196,6 +196,18 @@ def test_mc_fixes_beside_an_odd_blob(rollouts, what, monkeypatch):
     assert np.array_equal(col[ids], want.collided)
 
 
+def test_mc_map_that_fills_the_lds():
+    """10,220 blobs and the map's 20 boxes take the 160 KB of a workgroup to
+    the last byte."""
+    env = synth.plain2d(3, n=300)
+    assert env.box_lo.shape[0] == 20
+    rng = np.random.default_rng(2)
+    env = dataclasses.replace(env, goal_radius=0.4, blob_mu=rng.random((10220, 2)).astype(np.float32),
+                              blob_sigma=rng.uniform(0.02, 0.1, 10220).astype(np.float32),
+                              blob_amp=np.full(10220, 0.004, np.float32))
+    compare(env, None, np.array([0, 7], np.int32), rollouts=16, dt=0.05, speed=2.0)
+
+
 @pytest.mark.parametrize("speed", [1e18, 3e18, 1e20, 3e38])
 def test_mc_boxes_at_extreme_speed(speed):
     """Peak speeds whose eight steps (the distance within which a list of
