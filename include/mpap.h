@@ -529,8 +529,8 @@ int mpap_graph_add_boxes(const mpap_graph *g, int32_t n_boxes, const float *box_
  *   labels_expanded counts this call's expansions only; label ids of kept
  *   labels are prev's.
  * Errors: MPAP_ERR_INVAL (null, batches, different node counts, a judged or
- * early-stopped prev, sp unlike prev's search, early_stop or skip set, more
- * than 4096 iterations in prev), and as mpap_search.
+ * early-stopped prev, sp unlike prev's search, early_stop or skip set), and as
+ * mpap_search.
  */
 int mpap_search_update(const mpap_result *prev, const mpap_graph *g,
                        const mpap_search_params *sp, void *stream, mpap_result **out);

@@ -356,10 +356,6 @@ struct mpap_result {
     long long arena_labels = 0;  // arena size: expanded labels + goal plans closed at a stop
     unsigned long long pool_used = 0;  // bucket pool slots in use when the search ended
     long long reused_arena = 0;  // an update: arena ids taken over from the earlier result
-    // an update: arena id where each expanded group starts (earlier results'
-    // groups first), and the arena size last; empty for a plain search (its
-    // trace has the group sizes)
-    std::vector<long long> group_start;
     std::vector<int2> arena_host;  // filled on first mpap_label_path
     bool arena_loaded = false;
     bool ws_borrowed = false;  // ws belongs to a plan (valid until its next run)

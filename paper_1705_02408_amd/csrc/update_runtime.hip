@@ -232,23 +232,6 @@ __global__ void k_update_words(SearchArgs a) {
     }
 }
 
-// Where each group of the result's arena starts (parents are always in an
-// earlier group), and the arena size last: an update's stored list, else the
-// group sizes of the search's trace.  False when the trace was cut short.
-bool group_bounds(const mpap_result *r, std::vector<long long> &gs) {
-    if (!r->group_start.empty()) {
-        gs = r->group_start;
-        return gs.back() == r->arena_labels;
-    }
-    const int waves = r->stats.waves;
-    if (waves > kTraceCap || (long long)r->trace.size() < (long long)waves * kTraceWords)
-        return false;
-    gs.assign(waves + 1, 0);
-    for (int w = 0; w < waves; ++w)
-        gs[w + 1] = gs[w] + r->trace[(size_t)w * kTraceWords + kTrGroup];
-    return gs.back() == r->arena_labels;
-}
-
 template <typename T>
 int copy_d2d(T *dst, const T *src, size_t count, hipStream_t s) {
     if (count) HIP_TRY(hipMemcpyAsync(dst, src, sizeof(T) * count, hipMemcpyDeviceToDevice, s));
@@ -386,10 +369,8 @@ int mpap_search_update(const mpap_result *prev, const mpap_graph *gc,
     if (sp->heuristic != 0) return fail(MPAP_ERR_INVAL, "updates run on the analytic drift");
     if (prev->ws_borrowed)
         return fail(MPAP_ERR_INVAL, "a plan's result (search afresh or with mpap_search)");
-    std::vector<long long> gstart;
-    if (!group_bounds(prev, gstart) || prev->pool_used < 16)
-        return fail(MPAP_ERR_INVAL, "the earlier search ran more iterations than its trace "
-                                    "keeps (search afresh)");
+    if (prev->pool_used < 16)
+        return fail(MPAP_ERR_INVAL, "the earlier result holds no labels (search afresh)");
     SearchPrep p;
     int r = search_prep(g, sp, 1, p);
     if (r) return r;
@@ -501,14 +482,6 @@ int mpap_search_update(const mpap_result *prev, const mpap_graph *gc,
     if ((r = search_goal_finish(g, p, L, w, s, res, a, dev_out, ms, retries))) return bail(r);
     res->stats.labels_expanded = dev_out[kOutLabels] - La;  // this launch's expansions
     res->reused_arena = La;
-    // group bounds over the whole arena: the earlier ones, then this launch's
-    const int nw = res->stats.waves;
-    if (nw <= kTraceCap && (long long)res->trace.size() >= (long long)nw * kTraceWords) {
-        res->group_start = gstart;
-        for (int wv = 0; wv < nw; ++wv)
-            res->group_start.push_back(res->group_start.back() +
-                                       res->trace[(size_t)wv * kTraceWords + kTrGroup]);
-    }
     cleanup();
     *out = res;
     return MPAP_OK;

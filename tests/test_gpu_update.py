@@ -237,6 +237,38 @@ def test_update_of_long_rows_and_deep_plans(wide):
         d.close()
 
 
+def test_update_of_a_search_of_many_iterations():
+    """A chain of 5,000 nodes, an iteration each (more than the trace keeps):
+    an edge in its middle gets dearer, then one near its end, so that the second
+    update continues the first."""
+    n = 5000
+    edges = [(k, k + 1, 0.25, 0.0) for k in range(n - 1)]
+    edges += [(k, k + 2, 0.625, 0.0) for k in range(0, n - 2, 7)]
+    goal = np.zeros(n, dtype=np.uint8)
+    goal[-1] = 1
+    reset = np.zeros(n, dtype=np.uint8)
+    prev = old = None
+    for cut in (None, n // 2, n - 50):
+        if cut is not None:
+            edges[cut] = (cut, cut + 1, 0.5, 0.0)
+        d = upload(from_edges(n, edges, reset, goal))
+        fresh = mpap.mpap_search(d, 0.9, 2, 1.0, 0.25)
+        assert fresh.stats()["waves"] > 4096
+        if prev is not None:
+            upd = mpap.mpap_search_update(prev, d, 0.9, 2, 1.0, 0.25)
+            assert_same_fronts(upd, fresh, n, cut)
+            assert 0 < upd.stats()["labels_expanded"] < n - cut + 10
+            assert len(upd.path(int(upd.goal_front().label[0]))) > n // 2
+            prev.close()
+            old.close()
+            fresh.close()
+        else:
+            upd = fresh
+        prev, old = upd, d
+    prev.close()
+    old.close()
+
+
 def test_update_full_size_3d():
     """The 20,000-sample 3D workload (three objectives) after five obstacles
     are found: the update equals a fresh search."""
