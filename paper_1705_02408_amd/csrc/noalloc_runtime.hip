@@ -162,7 +162,7 @@ extern "C" int mpap_search_noalloc(const mpap_graph *gc, const mpap_search_param
     w.part_cnt = cv.take<long long>(2 * (size_t)L.full);
     w.part_open = cv.take<long long>(2 * (size_t)L.full);
     w.part_step = cv.take<long long>(2 * (size_t)L.full);
-    w.pool_top = cv.take<unsigned>(kBarWords);
+    w.pool_top = cv.take<unsigned>(1);
     w.bar = cv.take<unsigned>(kBarWords);
     w.err = cv.take<int>(1);
     w.out = cv.take<long long>(kOutWords);

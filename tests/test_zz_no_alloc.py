@@ -92,3 +92,18 @@ def test_noalloc_capacity_and_size_limits():
     assert ei.value.status == mpap.MPAP_ERR_INVAL
     assert "too large" in str(ei.value)
     big.close()
+
+
+def test_noalloc_takes_roadmaps_up_to_the_scratch():
+    """651,560 nodes: 96 bytes each and 0.36 MB of fixed words leave the 4 MiB
+    of the scratch that labels need, by 3.5 KB (256 workgroups)."""
+    n = 651_560
+    row_ptr = np.full(n + 1, 3, dtype=np.int32)
+    row_ptr[:3] = np.arange(3)
+    goal = np.zeros(n, np.uint8)
+    goal[3] = 1
+    dg = mpap.mpap_graph_from_csr(row_ptr, np.array([1, 2, 3], np.int32), np.ones(3, np.float32),
+                                  np.full(3, 0.25, np.float32), np.zeros(n, np.uint8), goal)
+    fr = mpap.mpap_search_noalloc(dg, 1.0, 2, 1.0, 0.5)
+    dg.close()
+    assert fr.vecs.tolist() == [[3.0, 0.75, 0.0]] and fr.goal_node.tolist() == [3]
