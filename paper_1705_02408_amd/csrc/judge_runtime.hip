@@ -185,7 +185,7 @@ int mpap_judge(mpap_result *r, float tol, int32_t fallback, void *stream, uint8_
     int rc = search_shape(p.stage_cap, p.block_threads, p.wave_min_targets, L, p.merge_halves);
     if (rc) return rc;
     L.obj = uniform_objectives(p);
-    fit_workgroups(L, g->n);
+    fit_workgroups(L, g);
     Workspace *w = nullptr;
     if ((rc = acquire_workspace(g, L, &w))) return rc;
     mpap_result *fb = new mpap_result();

@@ -1195,7 +1195,7 @@ int mpap_search_batch(const mpap_graph *gc, const mpap_search_params *sp, int32_
     if ((r = search_shape(p.stage_cap, p.block_threads, p.wave_min_targets, L, p.merge_halves)))
         return r;
     L.obj = uniform_objectives(p);
-    fit_workgroups(L, g->n);
+    fit_workgroups(L, g);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 
     Workspace *w = nullptr;

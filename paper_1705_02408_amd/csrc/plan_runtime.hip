@@ -242,7 +242,7 @@ int mpap_plan_create(mpap_graph *g, const mpap_search_params *sp, int32_t nsp,
                              p->shape, p->prep.merge_halves);
     if (!r) {
         p->shape.obj = uniform_objectives(p->prep);
-        fit_workgroups(p->shape, g->n);
+        fit_workgroups(p->shape, g);
     }
     auto bail = [&](int st) {
         mpap_plan_free(p);

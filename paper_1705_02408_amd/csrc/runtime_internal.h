@@ -454,15 +454,20 @@ inline bool wave_build(const SearchShape &L, int n) {
     return L.wcap > 0 &&
            (L.explicit_wmin || waves_first(L) || n >= 4 * (long long)wave_min(L));
 }
-// The workgroups of a search of n nodes: five eighths of the CUs where the
-// grid barriers (5.0 us on 256 workgroups, 3.1 on 128) weigh more than the
-// merges: two objectives below 65,536 nodes (6D of 50,000 states 8.7 ms, 9.6
-// on all CUs; 2D of 500 samples 1.42, 1.53; 3D of 20,000 samples 5.0 both ways;
-// 95,000 nodes of 32 queries 25.1, 21.5) and three below 1,024 (3D of 500
-// samples 0.98, 1.03; from 2,000 on all CUs are better).
-inline void fit_workgroups(SearchShape &L, int n) {
+// The workgroups of a search of g: five eighths of the CUs where the grid
+// barriers (5.0 us on 256 workgroups, 3.1 on 128) weigh more than the merges.
+// These grow with the nodes and with the labels a node keeps, about 25 on 2D
+// roadmaps, fewer in 3D, three in 6D.  Measured with two objectives on five
+// eighths / on all CUs (ms): 2D of 2,000 samples 3.52 / 3.60, 3,000 4.82 /
+// 4.62, 10,000 13.2 / 12.7, 50,000 88 / 73; 3D of 3,000 1.69 / 1.88, 12,000
+// 3.53 / 3.60, 15,000 4.20 / 4.20, 20,000 5.31 / 5.13, 60,000 15.1 / 12.7; 6D of
+// 10,000 6.4 / 7.2, 50,000 9.5 / 10.3; batches of 8,000 nodes 3.02 / 3.19, 16,000
+// 5.03 / 5.17, 26,000 8.94 / 8.85, 56,000 14.3 / 13.6, 95,000 25.1 / 21.5.  Three
+// objectives: 3D of 500 samples 0.98 / 1.03, from 2,000 on all CUs are better.
+inline void fit_workgroups(SearchShape &L, const mpap_graph *g) {
     if (L.threads != 1024 || L.wcap == 0 || L.explicit_wmin || L.halves_forced) return;
-    if (n < (L.obj == 2 ? 65536 : 1024)) L.nblocks = std::max(1, L.full * 5 / 8);
+    const int few = L.obj != 2 ? 1024 : g->dim == 2 ? 2560 : g->dim == 6 ? 65536 : 16384;
+    if (g->n < few) L.nblocks = std::max(1, L.full * 5 / 8);
 }
 // The search build for a launch on g (see search_kernels.h).
 inline const void *search_kernel_for(const SearchShape &L, int n) {

@@ -649,6 +649,27 @@ def test_workgroups_by_size(n, n_obj, share):
         dg.close()
 
 
+@pytest.mark.parametrize("dim,n,share", [(2, 2558, 5), (2, 2559, 8), (3, 16382, 5), (3, 16383, 8),
+                                            (6, 16383, 5)])
+def test_workgroups_of_built_roadmaps(dim, n, share):
+    """Two objectives: the number of nodes from which all workgroups run, by
+    the roadmap's dimension (the root is one more node); the same fronts as
+    with merges by halves on all of them."""
+    env = (synth.plain2d if dim == 2 else synth.plain3d if dim == 3 else synth.plain6d)(4, n=n)
+    env = dataclasses.replace(env, goal=env.pos[-1][:min(dim, 3)].copy(), goal_radius=0.1)
+    dg = mpap.mpap_build_graph(env)
+    res = mpap.mpap_search(dg, env.beta, 2, env.radius, env.lam)
+    ref = mpap.mpap_search(dg, env.beta, 2, env.radius, env.lam, merge_halves=8192)
+    assert (res.stats()["blocks"], ref.stats()["blocks"]) == (256 * share // 8, 256)
+    assert (res.stats()["wave_build"], ref.stats()["wave_build"]) == (1, 0)
+    assert res.goal_front().vecs.shape[0] > 0
+    assert np.array_equal(bits(res.goal_front().vecs), bits(ref.goal_front().vecs))
+    for v in range(0, n + 1, 11):
+        assert np.array_equal(bits(res.node_front(v)), bits(ref.node_front(v))), v
+    for x in (res, ref, dg):
+        x.close()
+
+
 @pytest.mark.parametrize("n_obj,wave", [(2, 1), (3, 0)])
 def test_default_build_by_objectives(n_obj, wave):
     """Two-objective searches merge by single waves where an iteration has
