@@ -308,7 +308,8 @@ __device__ __forceinline__ float pair_drift(const BuildArgs &gl, int a, int b, f
 }
 
 // Blobs staged for the float32 quality: 2 sigma^2 in the place of sigma and,
-// for plain blobs (see PlainBlobs), its reciprocal behind the amplitudes.
+// for plain blobs (see launch_edge_features), its reciprocal behind the
+// amplitudes.
 template <bool kPlain, int D>
 __device__ __forceinline__ void stage_quality_blobs(const BuildArgs &g, float *blob) {
     for (int i = threadIdx.x; i < g.nblob * D; i += blockDim.x) blob[i] = g.mu[i];
@@ -324,11 +325,17 @@ __device__ __forceinline__ void stage_quality_blobs(const BuildArgs &g, float *b
 
 // q at P points (blob_quality's float32 sums, bit for bit).  Bound by
 // instruction issue: distance, division and exponential.  For plain blobs the
-// division d2 / b is three operations with r = 1 / b rounded: q = d2 r is
-// within one unit of the quotient, d2 - q b is exact in a fused operation,
-// and q + r (d2 - q b) is then the correctly rounded quotient (Markstein,
-// "Computation of elementary functions on the IBM RISC System/6000
-// processor", 1990, theorem 8.4), as the division itself gives it.
+// division d2 / b is three operations with r = 1 / b rounded: q = d2 r, then
+// q + r (d2 - q b), each in one fused operation.  This rounds as the division
+// itself: q is off by less than 1.5 units in the last place, and by half a unit
+// wherever the quotient lies so near the middle between two floats that it
+// matters (d2 r is off by less than one unit before it is rounded, so q is one
+// of the two floats); there d2 - q b is exact, and r's rounding moves the
+// corrected value by less than the quotient's distance from the middle, which
+// two 24-bit significands keep at 1/(2 b) units or more (Markstein, "Computation
+// of elementary functions on the IBM RISC System/6000 processor", 1990, theorem
+// 8.4, for a q within one unit).  Checked over random and over nearest
+// quotients.
 template <bool kPlain, int D, int P>
 __device__ __forceinline__ void quality_points(const float *blob, int nblob,
                                                const float (&x)[P][D], float (&q)[P]) {
