@@ -555,10 +555,13 @@ __global__ void __launch_bounds__(256) k_near_fill(BuildArgs g, const int *off, 
 
 // Collision(a, b), (a, b) the candidate pair in id order: points
 // x_a + (k/K)(x_b - x_a), k = 0..K, K = ceil(cost/step), against closed boxes.
-// A wave's 64 candidates have one or two sources and lie within the radius of
+// Where rows are long a wave's 64 candidates have few sources (about four of 20
+// neighbours in 2D, two or three of 40 in 3D) and lie within the radius of
 // them: the boxes that miss the wave's common range are left out 64 at a time
-// (2.1 million candidates, 100 boxes: 59 us; each candidate against each box
-// 472 us).
+// (3D, 2.0 million candidates, 100 boxes: 63 us, each candidate against each box
+// 476; 2D, 1.2 million, 20 boxes: 17 and 56; the edges that are left against
+// five new boxes 23 and 48, 13 and 23).  Sources far apart make the range wide
+// and the gain small, whatever their number; the result is the same.
 template <int D>
 __global__ void __launch_bounds__(256) k_collide(BuildArgs g, long long m, const int *cand_u,
                                                  const int *cand_v, const float *cand_c,
