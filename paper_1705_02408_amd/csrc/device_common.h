@@ -133,6 +133,13 @@ __device__ __forceinline__ float block_min(float v, float *scratch) {
 // L2 contents) and, once all blocks have arrived, drops stale lines
 // (agent-scope acquire) before the workgroup goes on.  The waves of a
 // workgroup share one CU and its L1, so the one invalidation serves them all.
+// The last block of a group goes on to the root, and the last there to the
+// release words, without an acquire in between, so in the memory model's terms
+// the releases of the other blocks don't pass from word to word.  It rests on
+// the hardware: a block's agent-scope release has completed its write-back
+// before the block's arrival is issued, so once an arrival is seen, by whatever
+// chain of words, its data is past the L2 of its XCD, and an acquire after
+// that reads it.
 //
 // Atomics on one address are served one after the other (about 12 ns each
 // across XCDs) and wait behind the polls of that line.  So blocks arrive in
