@@ -441,9 +441,13 @@ inline bool waves_first(const SearchShape &L) {
     return L.obj == 2 && L.threads == 1024 && !L.halves_forced;
 }
 // The least targets of an iteration that merges by single waves, where they
-// are not the rule: four waves a target for two objectives, a quarter of one
-// for three, whose children scan prefixes of the front (3D of 20,000 samples
-// 19.5 ms against 12.4).
+// are not the rule.  Two objectives (256- and 512-thread workgroups): a target
+// for four waves of the grid; with four targets a wave instead, 6D of 50,000
+// states takes 18.1 ms for 11.7 with 512 threads, of 20,000 16.1 for 14.1 with
+// 256 and 12.0 for 9.6 with 512, 3D of 20,000 samples 6.8 for 6.7 and 5.6 for
+// 5.1, but 2D of 10,000 samples 20.8 for 25.2 and 12.3 for 13.9.  Three: four
+// targets a wave, since their children scan prefixes of the front (3D of 20,000
+// samples 19.5 ms by waves, 12.4 by halves).
 inline int wave_min(const SearchShape &L) {
     const int waves = L.nblocks * (L.threads / 64);
     if (L.explicit_wmin) return L.wmin;
