@@ -314,8 +314,8 @@ typedef struct {
     int32_t lds_front_cap;    /* largest per-node front the LDS merge stages */
     int32_t blocks;           /* workgroups of the persistent launch */
     int32_t max_front;        /* largest final per-node front */
-    int32_t wave_build;       /* 1: the kernel build with single-wave merges ran (in
-                                 iterations with many small targets), 0: the weight-ordered one */
+    int32_t wave_build;       /* 1: the kernel build with single-wave merges ran (light
+                                 targets of iterations with enough of them), 0: another */
     int32_t judged_failed;    /* queries whose learned-drift front mpap_judge rejected */
     float fallback_ms;        /* device time of the analytic re-search of those queries */
     int32_t half_front_cap;   /* front stage of a half workgroup when merges ran by halves

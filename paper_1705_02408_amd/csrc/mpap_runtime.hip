@@ -119,8 +119,8 @@ int mpap_graph_from_csr(int32_t n, const int32_t *row_ptr, const int32_t *col,
 // ------------------------------------------------------------- graph build
 }  // extern "C"
 
-// Double-integrator roadmap: steering selection, compaction, drift on the
-// device; the in-edge lists are built by the import path.
+// Double-integrator roadmap: steering selection, compaction, drift, in-edge
+// rows, goal list and the checks of the values on the device.
 static int build_graph6(const mpap_env *env, const mpap_graph_params *gp, void *stream,
                         mpap_graph **out) {
     const int n = env->n_nodes;

@@ -24,8 +24,8 @@ constexpr int kErrTarget = 8;   // a queued merge target is not a node (internal
 constexpr int kWeightClasses = 10;
 constexpr int kWeightClassBase = 128;
 // Most children of a target that one wave merges; above, a whole workgroup
-// (32 planar and spatial queries at once: 25.7 ms at 32, 22.9 at 64, 21.8 at
-// 128, 23.4 at 256; a spatial roadmap of 20,000 samples 6.3, 5.7, 5.1, 4.7 ms).
+// (32 planar and spatial queries of 95,000 nodes at once: 25.7 ms at 32, 22.9
+// at 64, 21.8 at 128, 23.4 at 256; a spatial roadmap of 20,000 samples 6.3, 5.7, 5.1, 4.7 ms).
 constexpr int kWaveChildren = 128;
 // With few targets a workgroup there are waves to spare, and the slowest merge
 // sets the pace: at most this many children for each target a workgroup has
