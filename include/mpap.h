@@ -162,12 +162,13 @@ typedef struct {
                               1024 (one per CU), 512 (two) or 256 (four); 0 = 1024.
                               Never changes the result. */
     int32_t wave_min_targets; /* tuning: an iteration with at least this many merge
-                                 targets merges those of small front and few new
-                                 children with a single wave each (16 merges per CU at
-                                 once); 0 = any iteration with more targets than
-                                 workgroups when all queries have two objectives, else
-                                 four times the waves of the grid; < 0 = never.  Never
-                                 changes the result. */
+                                 targets, and more than workgroups, merges those of
+                                 small front and few new children with a single wave
+                                 each (16 merges per CU at once); 0 = any iteration
+                                 with more targets than workgroups when all queries
+                                 have two objectives (below 1024 threads: a target for
+                                 four waves of the grid), else four targets a wave;
+                                 < 0 = never.  Never changes the result. */
     int32_t skip;             /* 1: leave this query out of a batched search (its root
                                  label is not seeded; its goal front is empty); 0 =
                                  search it */
